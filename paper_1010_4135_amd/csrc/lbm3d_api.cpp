@@ -199,7 +199,7 @@ int32_t solver_create(const lbm3d_params* p, lbm3d_solver** out)
 }
 
 // One time step of a solve: fused update f[cur] -> f[cur^1], then the
-// boundary layers of the new level.
+// boundary layers of the new level that the next step reads from memory.
 static hipError_t enqueue_one(lbm3d_solver* h, int cur, hipStream_t s)
 {
     hipError_t e = launch_step(h->mode, h->g, h->bc, h->tile, h->md, h->mf, h->p.inflow, h->f[cur], h->f[cur ^ 1],
@@ -241,11 +241,13 @@ int32_t solver_enqueue_steps(lbm3d_solver* h, int64_t nsteps)
         HIPCHK(hipGraphLaunch(ge, s));
         left -= GRAPH_STEPS;
         h->steps += GRAPH_STEPS;
+        if (h->tile.by == 0) h->layers_stale = true;
     }
     for (; left > 0; left--) {
         HIPCHK(enqueue_one(h, h->cur, s));
         h->cur ^= 1;
         h->steps++;
+        if (h->tile.by == 0) h->layers_stale = true;
     }
     return LBM3D_OK;
 }
@@ -335,6 +337,7 @@ int32_t lbm3d_init(lbm3d_t h, const double* rho, const double* ux, const double*
     HIPCHK(hipStreamSynchronize(s));
     h->cur = 0;
     h->steps = 0;
+    h->layers_stale = false;
     h->initialised = true;
     return LBM3D_OK;
 }
@@ -383,6 +386,7 @@ int32_t lbm3d_step_profiled(lbm3d_t h, int64_t nsteps, double* total_ms, double*
         if (e == hipSuccess) {
             h->cur ^= 1;
             h->steps++;
+            if (h->tile.by == 0) h->layers_stale = true;
         }
     }
     if (e == hipSuccess) e = hipEventRecord(h->ev1, s);
@@ -413,10 +417,11 @@ static int32_t set_launch(lbm3d_t h, const TileCfg& t)
             h->graph_exec[k] = nullptr;
         }
     h->tile = t;
-    // the layers a tiled step forms itself are not kept in memory: refresh
-    // them all, so any launch shape can take over
+    // the layers a step forms itself are not kept in memory: refresh them
+    // all, so any launch shape can take over
     if (h->initialised) {
         HIPCHK(launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, true, h->f[h->cur], h->stream));
+        h->layers_stale = false;
         HIPCHK(hipStreamSynchronize(h->stream));
     }
     return LBM3D_OK;
@@ -543,6 +548,7 @@ int32_t lbm3d_set_f(lbm3d_t h, const void* host, size_t bytes)
     if (e == hipSuccess) e = launch_pack(h->mode, h->g, h->f[h->cur], dense, false, s);
     if (e == hipSuccess)
         e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, true, h->f[h->cur], s);
+    if (e == hipSuccess) h->layers_stale = false;
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(dense);
     return dev_err(e);

@@ -22,6 +22,8 @@ struct lbm3d_solver {
     double* out5 = nullptr;
     uint32_t* health = nullptr;
     int nred = 0;
+    bool layers_stale = false; // the current level's boundary layers in memory are an older level's: the
+                               // untiled kernel forms layers itself, the tiled ones read some from memory
     bool upwind2 = false;      // the second-order upwind variant (steps untiled)
     int cur = 0;               // buffer holding the current level
     int64_t steps = 0;

@@ -317,7 +317,16 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
     const size_t cb = hcount_.size() * sizeof(BatchCount);
     dcount_ = (BatchCount*)((char*)dblockjob_ + align256(bb));
     dhealth_ = (uint32_t*)((char*)dcount_ + align256(cb));
-    hipError_t e = hipMemcpyAsync(dsolves_, table.data(), sb, hipMemcpyHostToDevice, s);
+    // the tiles read some layers from memory, which members that last
+    // stepped alone and untiled have left behind
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < members.size() && e == hipSuccess; k++) {
+        lbm3d_solver* h = members[k];
+        if (!h->layers_stale) continue;
+        e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[h->cur], s, ghost_rest_[k]);
+        if (e == hipSuccess) h->layers_stale = false;
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(dsolves_, table.data(), sb, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(dtiles_, plan_.tiles.data(), tb, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(dqueue_, &plan_.queue, sizeof(BatchQueue), hipMemcpyHostToDevice, s);
     if (e == hipSuccess && lb) e = hipMemcpyAsync(dlayers_, ljobs.data(), lb, hipMemcpyHostToDevice, s);
@@ -430,12 +439,6 @@ int32_t BatchPlan::run(int64_t k, hipStream_t s, bool graphs, const std::vector<
         if (n == 0) continue;
         h->steps += n;
         if (n & 1) h->cur ^= 1;
-        // a member that steps alone untiled reads every layer from memory:
-        // refresh the ones the tiled batch kernel formed itself
-        if (h->tile.by == 0) {
-            e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[h->cur], s);
-            if (e != hipSuccess) return herr(e);
-        }
     }
     return LBM3D_OK;
 }

@@ -13,99 +13,10 @@ namespace lbm3d {
 // One explicit step of Eq. (lp) with NND convection at every interior node:
 //   f_i^{n+1} = f_i - dt/dx sum_a v_ia (g_{I+1/2} - g_{I-1/2})
 //               - dt/tau (f_i - f_i^eq) + lambda_i dt/dx^2 sum_a (f_{I+1} - 2 f_I + f_{I-1})
-// reading every term at level n (forward Euler, Eq. (fi1)).  The boundary
-// layers of f^n hold valid values, so every neighbour load is in bounds.
-// This one-node-per-thread kernel and the tiled one evaluate the same
-// operations per node (node_update and the NND helpers), so they agree
-// bitwise.
-template <int I, bool U2, typename S, typename C>
-__device__ __forceinline__ void update_one(const S* __restrict__ fi, S* __restrict__ fo, int64_t site,
-                                           const int64_t (&xo)[4], int64_t sy, int64_t sz, C f0, C feq,
-                                           const Model<C>& m)
-{
-    constexpr int SG[3] = {vsign(I, 0), vsign(I, 1), vsign(I, 2)};
-    constexpr int G = vgroup(I);
-    // neighbour at distance d (-2, -1, 1, 2) along axis a: x neighbours
-    // through the per-thread offsets xo (which reach the x layers), y and z
-    // neighbours by stride
-    auto nb = [&](int a, int d) {
-        const int64_t o = a == 0 ? xo[d < 0 ? d + 2 : d + 1] : site + d * (a == 1 ? sy : sz);
-        return static_cast<C>(fi[o]);
-    };
-    C D[3] = {C(0), C(0), C(0)}, L[3] = {C(0), C(0), C(0)};
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        if (SG[a] > 0) {
-            const C fm2 = nb(a, -2), fm1 = nb(a, -1), fp1 = nb(a, 1);
-            const C e0 = f0 - fm1, e1 = fp1 - f0;
-            D[a] = U2 ? up2_pos(fm1 - fm2, e0) : nnd_pos(fm1 - fm2, e0, e1);
-            L[a] = e1 - e0;
-        } else if (SG[a] < 0) {
-            const C fm1 = nb(a, -1), fp1 = nb(a, 1), fp2 = nb(a, 2);
-            const C e0 = f0 - fm1, e1 = fp1 - f0;
-            D[a] = U2 ? up2_neg(e1, fp2 - fp1) : nnd_neg(e0, e1, fp2 - fp1);
-            L[a] = e1 - e0;
-        } else if (G <= 1) {
-            L[a] = nb(a, -1) + nb(a, 1);
-        }
-    }
-    fo[site] = static_cast<S>(node_update<I, C>(f0, feq, D[0], D[1], D[2], L[0], L[1], L[2], m));
-}
-
-template <bool U2, typename S, typename C, int I = 0>
-__device__ __forceinline__ void update_all(const S* __restrict__ f, S* __restrict__ fn, int64_t site,
-                                           const int64_t (&xo)[4], int64_t sv, int64_t sy, int64_t sz,
-                                           const C (&fc)[NV], const C (&feq)[NV], const Model<C>& m)
-{
-    if constexpr (I < NV) {
-        update_one<I, U2, S, C>(f + I * sv, fn + I * sv, site, xo, sy, sz, fc[I], feq[I], m);
-        update_all<U2, S, C, I + 1>(f, fn, site, xo, sv, sy, sz, fc, feq, m);
-    }
-}
-
-// Offsets (within a velocity plane) of the x neighbours at distance -2, -1,
-// +1, +2 of node (x, y, z) at `site`: along the row, or in the x-layer block
-// for those beyond a face when rows are dense.
-__device__ __forceinline__ void x_offsets(const Grid& g, int x, int y, int z, int64_t site, int64_t (&xo)[4])
-{
-    const int d[4] = {-2, -1, 1, 2};
-    const int64_t row = g.xg + (int64_t)(z + NG) * g.xgz + (int64_t)(y + NG) * 4;
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const int xx = x + d[k];
-        const bool out = g.xg != 0 && (xx < 0 || xx >= g.nx);
-        const int64_t layer = xx < 0 ? xx + 2 : 2 + (xx - g.nx);  // 0: -2, 1: -1, 2: nx, 3: nx+1
-        xo[k] = out ? row + layer : site + d[k];
-    }
-}
-
-// U2: the second-order upwind variant in place of NND (untiled only).
-template <int MODE, bool U2>
-__global__ void __launch_bounds__(TX * TY)
-k_step(Grid g, Model<double> md, Model<float> mf, const typename Types<MODE>::S* __restrict__ f,
-       typename Types<MODE>::S* __restrict__ fn, uint32_t* __restrict__ health)
-{
-    using S = typename Types<MODE>::S;
-    using C = typename Types<MODE>::C;
-    using M = typename Types<MODE>::M;
-    const int x = blockIdx.x * TX + threadIdx.x;
-    const int y = blockIdx.y * TY + threadIdx.y;
-    const int z = blockIdx.z;
-    if (x >= g.nx || y >= g.ny) return;
-    const Model<C>& mc = pick<C>(md, mf);
-    const Model<M>& mm = pick<M>(md, mf);
-    const int64_t site = g.org + (int64_t)z * g.sz + (int64_t)y * g.sy + x;
-    C fc[NV];
-#pragma unroll
-    for (int i = 0; i < NV; i++) fc[i] = static_cast<C>(f[i * g.sv + site]);
-    const Macro<M> q = moments<M, C>(fc, mm);
-    report_health(health, health_bits(q));
-    C feq[NV];
-    equilibrium<C, M>(q, mm, mc, feq);
-    int64_t xo[4];
-    x_offsets(g, x, y, z, site, xo);
-    update_all<U2, S, C>(f, fn, site, xo, g.sv, g.sy, g.sz, fc, feq, mc);
-}
+// reading every term at level n (forward Euler, Eq. (fi1)).  The tiled
+// kernel (lbm3d_tile.h) and the untiled one (lbm3d_block.h)
+// evaluate the same operations per node (the NND helpers and update terms
+// of lbm3d_model.h), so they agree bitwise.
 
 // Tiled fused step: one workgroup per 64 x BY x TZ tile (see lbm3d_tile.h).
 
@@ -533,26 +444,6 @@ static void launch_tiled(const Grid& g, const FaceBC& bc, int tz, bool stream, c
     }
 }
 
-template <int MODE>
-static void launch_untiled(dim3 grid, dim3 block, bool upwind2, const Grid& g, const Model<double>& md,
-                           const Model<float>& mf, const void* f, void* fn, uint32_t* health, hipStream_t s,
-                           hipEvent_t e0, hipEvent_t e1)
-{
-    using S = typename Types<MODE>::S;
-    const S* fi = (const S*)f;
-    S* fo = (S*)fn;
-    if (e0 || e1) {
-        if (upwind2)
-            hipExtLaunchKernelGGL(k_step<MODE, true>, grid, block, 0, s, e0, e1, 0, g, md, mf, fi, fo, health);
-        else
-            hipExtLaunchKernelGGL(k_step<MODE, false>, grid, block, 0, s, e0, e1, 0, g, md, mf, fi, fo, health);
-    } else if (upwind2) {
-        k_step<MODE, true><<<grid, block, 0, s>>>(g, md, mf, fi, fo, health);
-    } else {
-        k_step<MODE, false><<<grid, block, 0, s>>>(g, md, mf, fi, fo, health);
-    }
-}
-
 hipError_t launch_step(int mode, const Grid& g, const FaceBC& bc, const TileCfg& tc, const Model<double>& md,
                        const Model<float>& mf, const double (*inflow)[5], const void* f, void* fn,
                        uint32_t* health, hipStream_t s, bool upwind2, hipEvent_t e0, hipEvent_t e1)
@@ -576,8 +467,7 @@ hipError_t launch_step(int mode, const Grid& g, const FaceBC& bc, const TileCfg&
         }
         return hipGetLastError();
     }
-    const dim3 grid((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, g.nz), block(TX, TY);
-    LBM3D_DISPATCH(mode, launch_untiled<MD>(grid, block, upwind2, g, md, mf, f, fn, health, s, e0, e1));
+    launch_block(mode, g, bc, md, mf, inflow, f, fn, health, s, upwind2, e0, e1);
     return hipGetLastError();
 }
 

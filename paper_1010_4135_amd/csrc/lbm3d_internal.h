@@ -140,9 +140,9 @@ bool tile_supported(int mode, const Grid& g, const TileCfg& t);
 bool tiled_fits(int mode, const Grid& g);
 // Faces whose boundary layers the boundary-layer kernel refreshes after
 // every step.  Fixed-state layers are written once at init.  The tiled
-// kernels form the x layers themselves when 64-wide tiles cover x exactly
-// (nx a multiple of 64) and wrap periodic faces, so with `tiled` those
-// faces need no layers in memory.
+// kernels form the x layers themselves (but the +x ones of a one-column
+// tail) and wrap periodic faces, so with `tiled` only the other faces need
+// layers in memory; the untiled kernel forms every layer itself.
 uint32_t ghost_faces(const Grid& g, const FaceBC& bc, bool tiled);
 // upwind2: the second-order upwind variant (untiled kernel only: tc.by == 0)
 // ev_start / ev_stop (optional): events that the kernel's own dispatch
@@ -152,6 +152,10 @@ hipError_t launch_step(int mode, const Grid& g, const FaceBC& bc, const TileCfg&
                        const Model<float>& mf, const double (*inflow)[5], const void* f, void* fn,
                        uint32_t* health, hipStream_t s, bool upwind2 = false, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
+// The untiled kernel's launch (launch_step with tc.by == 0).
+void launch_block(int mode, const Grid& g, const FaceBC& bc, const Model<double>& md, const Model<float>& mf,
+                  const double (*inflow)[5], const void* f, void* fn, uint32_t* health, hipStream_t s, bool upwind2,
+                  hipEvent_t ev_start, hipEvent_t ev_stop);
 // (rho, ux, uy, uz, T) of the two x faces' fixed states, from the ABI's
 // (rho, ux, uy, uz, p)
 void x_fixed_states(const double (*inflow)[5], double (&xin)[2][5]);
@@ -184,9 +188,7 @@ hipError_t launch_batch_step(int mode, int by, bool stream, const BatchSolve* so
                              BatchQueue* queue, int nlists, int nblocks, int parity, const BatchCount* counts,
                              hipStream_t s);
 
-// block shape of the untiled step kernel; x extent of a tile of the tiled one;
-// block size of the conservation reduction
-constexpr int TX = 64, TY = 4;
+// block size of the conservation reduction; x extent of a tile of the tiled step
 constexpr int RB = 256;
 constexpr int TILE_X = 64;
 // Lanes of the tiled step outside the grid store unconditionally into a sink

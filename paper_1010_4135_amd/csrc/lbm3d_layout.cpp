@@ -169,14 +169,15 @@ bool tile_supported(int mode, const Grid& g, const TileCfg& t)
 uint32_t ghost_faces(const Grid& g, const FaceBC& bc, bool tiled)
 {
     uint32_t m = 0;
+    if (!tiled) return m;
     for (int face = 0; face < 6; face++) {
         const int kind = bc.kind[face];
         if (kind == BC_INFLOW) continue;
         // the tiles form the -x layers, and the +x layers unless the last
         // tile holds a single column (see x_forms)
-        if (tiled && face == 0) continue;
-        if (tiled && face == 1 && g.nx % TILE_X != 1) continue;
-        if (tiled && kind == BC_PERIODIC) continue;
+        if (face == 0) continue;
+        if (face == 1 && g.nx % TILE_X != 1) continue;
+        if (kind == BC_PERIODIC) continue;
         m |= 1u << face;
     }
     return m;
