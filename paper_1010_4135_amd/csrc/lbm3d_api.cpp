@@ -210,9 +210,22 @@ static hipError_t enqueue_one(lbm3d_solver* h, int cur, hipStream_t s)
     return launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[cur ^ 1], s, rest);
 }
 
+// Before steps of the tiled kernel: the layers it reads from memory, if the
+// solve last stepped untiled (as a member of a batch; lbm3d_set_tile
+// refreshes them itself).
+static hipError_t refresh_layers(lbm3d_solver* h)
+{
+    if (!h->layers_stale || h->tile.by == 0) return hipSuccess;
+    const hipError_t e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[h->cur], h->stream,
+                                       ghost_faces(h->g, h->bc, true));
+    if (e == hipSuccess) h->layers_stale = false;
+    return e;
+}
+
 int32_t solver_enqueue_steps(lbm3d_solver* h, int64_t nsteps)
 {
     hipStream_t s = h->stream;
+    if (nsteps > 0) HIPCHK(refresh_layers(h));
     int64_t left = nsteps;
     // runs of GRAPH_STEPS steps are replayed from a graph captured once per
     // starting buffer (the step count is even, so the run ends where it began)
@@ -373,6 +386,7 @@ int32_t lbm3d_step_profiled(lbm3d_t h, int64_t nsteps, double* total_ms, double*
     for (auto& x : ev)
         if (e == hipSuccess) e = hipEventCreate(&x);
     hipStream_t s = h->stream;
+    if (e == hipSuccess) e = refresh_layers(h);
     if (e == hipSuccess) e = hipEventRecord(h->ev0, s);
     for (int64_t k = 0; k < nsteps && e == hipSuccess; k++) {
         const int c = h->cur;

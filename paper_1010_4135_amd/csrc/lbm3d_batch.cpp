@@ -7,6 +7,8 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <functional>
+#include <map>
 #include <mutex>
 #include <new>
 #include <set>
@@ -124,48 +126,77 @@ int32_t plan_tiles(const std::vector<Grid>& grids, int by, int tz, int cus, Tile
 BatchPlan::~BatchPlan()
 {
     if (last_stream_) (void)hipStreamSynchronize(last_stream_);
-    release_graph();
+    release_graphs();
     if (capture_stream_) (void)hipStreamDestroy(capture_stream_);
     if (dmem_) (void)hipFree(dmem_);
 }
 
-void BatchPlan::release_graph()
+void BatchPlan::release_graphs()
 {
-    // (callers have drained the stream the graph was launched on)
-    if (graph_) (void)hipGraphExecDestroy(graph_);
-    graph_ = nullptr;
+    // (callers have drained the stream the graphs were launched on)
+    for (Group& q : groups_)
+        if (q.graph) (void)hipGraphExecDestroy(q.graph);
+    groups_.clear();
 }
 
-// Tile depth from a launch model of a membership: the persistent
-// workgroups share the tiles' work (each tile's planes plus the planes its
-// z ring loads first), and no launch ends before its longest tile.  The
-// depth (16, 32, ... up to whole columns) with the lowest estimate wins,
-// the deeper one on a tie: whole columns for a batch as large as the
-// 64-solve mix (as the tuner finds), short chunks for a few solves, whose
-// whole columns would leave most compute units idle.
+// Planes the busiest compute unit marches when the tiles of a membership at
+// depth d are dealt out longest first, each to the unit that is free first
+// (as the persistent workgroups take them): each tile its planes plus the
+// ones its z ring loads first.
+static double tile_makespan(const std::vector<Grid>& grids, int by, int d, int cus)
+{
+    std::map<int, int64_t, std::greater<int>> tiles;  // by depth
+    for (const Grid& g : grids) {
+        const int64_t cols = (int64_t)((g.nx + TILE_X - 1) / TILE_X) * ((g.ny + by - 1) / by);
+        if (g.nz / d) tiles[d] += cols * (g.nz / d);
+        if (g.nz % d) tiles[g.nz % d] += cols;
+    }
+    std::map<double, int64_t> units{{0.0, (int64_t)cus}};  // compute units by the planes they have
+    double last = 0.0;
+    for (const auto& t : tiles) {
+        const double cost = t.first + TILE_PROLOGUE_PLANES;
+        int64_t left = t.second;
+        // (whole rounds over all units at once)
+        const int64_t rounds = left / cus - 1;
+        if (rounds > 0) {
+            std::map<double, int64_t> moved;
+            for (const auto& u : units) moved[u.first + (double)rounds * cost] = u.second;
+            units.swap(moved);
+            left -= rounds * cus;
+        }
+        while (left > 0) {
+            const auto u = units.begin();
+            const double load = u->first;
+            const int64_t n = std::min(left, u->second);
+            if ((u->second -= n) == 0) units.erase(u);
+            units[load + cost] += n;
+            left -= n;
+        }
+    }
+    for (const auto& u : units) last = std::max(last, u.first);
+    return last;
+}
+
+// Tile depth of a membership: of 16, 32, ... up to whole columns, the
+// deepest whose makespan is within 5% of the shortest: whole columns for a
+// batch as large as the 64-solve mix (as the tuner finds), short chunks for
+// a few solves, whose whole columns would leave most compute units idle.
 static int model_depth(const std::vector<Grid>& grids, int by, int cus)
 {
     int maxnz = 1;
     for (const Grid& g : grids) maxnz = std::max(maxnz, g.nz);
-    int best = 0;
-    double best_t = 0.0;
+    std::vector<std::pair<int, double>> tried;
+    double best = 0.0;
     for (int d = 16;; d *= 2) {
         const int dd = std::min(d, maxnz);
-        double work = 0.0, longest = 0.0;
-        for (const Grid& g : grids) {
-            const double cols = (double)((g.nx + TILE_X - 1) / TILE_X) * ((g.ny + by - 1) / by);
-            const double chunks = (double)((g.nz + dd - 1) / dd);
-            work += cols * (g.nz + TILE_PROLOGUE_PLANES * chunks);
-            longest = std::max(longest, std::min(dd, g.nz) + TILE_PROLOGUE_PLANES);
-        }
-        const double t = std::max(work / cus, longest);
-        if (best == 0 || t <= best_t) {
-            best = dd;
-            best_t = t;
-        }
+        tried.emplace_back(dd, tile_makespan(grids, by, dd, cus));
+        if (tried.size() == 1 || tried.back().second < best) best = tried.back().second;
         if (dd >= maxnz) break;
     }
-    return best;
+    int depth = maxnz;
+    for (const auto& t : tried)
+        if (t.second <= 1.05 * best) depth = t.first;
+    return depth;
 }
 
 // Tile depth of a plan: tz > 0 as given; 0: the precision's tuned depth,
@@ -181,17 +212,107 @@ static int plan_depth(int mode, int tz, const std::vector<Grid>& grids, int by, 
     return model_depth(grids, by, cus);
 }
 
-// layer jobs of the members (faces the tiles leave to memory)
-static void layer_jobs(const std::vector<lbm3d_solver*>& members, std::vector<uint32_t>& rest,
-                       std::vector<BatchLayerJob>& ljobs, std::vector<int32_t>& block_job, int& nlblocks)
+// Members are independent, so a run steps them group by group, all its steps
+// for one group before the next: a group whose two levels fit the 256 MB
+// memory-side cache steps from there instead of from HBM.  The bytes a step
+// touches are 30 values per node; GROUP_BYTES leaves room for the uneven
+// spread of several members' pages over the cache (six 64^3 solves in FP32
+// with FP64 moments, 189 MB, run at 39.5 G node updates/s, seven at 32.7,
+// eight at 28.4), a member alone may fill it (128^3, 252 MB: 40).  Such
+// groups are stepped by the untiled kernel, whose blocks fill the device at
+// once and form their own boundary layers: a small solve has few tiles, each
+// a long serial march (one 64^3 solve 53.9 us a step tiled, 11.6 untiled;
+// 128^3 bubble 65.3 and 55).  Larger members form one group of their own,
+// stepped by the tiled kernel: from HBM it streams faster than the blocks,
+// which read their z neighbours several times (256x128x128: 114 us against
+// 150).
+constexpr int64_t GROUP_BYTES = (int64_t)192 << 20, ALONE_BYTES = (int64_t)256 << 20;
+
+struct GroupMembers {
+    std::vector<int32_t> who;
+    int64_t bytes = 0;
+    bool tiled = false;
+};
+
+static std::vector<GroupMembers> group_members(const std::vector<lbm3d_solver*>& members)
 {
-    rest.assign(members.size(), 0u);
+    std::vector<GroupMembers> out;
+    GroupMembers large;
+    large.tiled = true;
+    std::vector<std::pair<int64_t, int32_t>> fits;
+    for (size_t k = 0; k < members.size(); k++) {
+        const int64_t b = members[k]->n * 2 * NV * (int64_t)elem_size(members[k]->mode);
+        if (b > ALONE_BYTES)
+            large.who.push_back((int32_t)k);
+        else
+            fits.emplace_back(-b, (int32_t)k);
+    }
+    // largest first, each into the fullest group it fits
+    std::stable_sort(fits.begin(), fits.end(),
+                     [](const auto& a, const auto& b) { return a.first < b.first; });
+    for (const auto& m : fits) {
+        GroupMembers* best = nullptr;
+        for (GroupMembers& q : out)
+            if (q.bytes - m.first <= GROUP_BYTES && (!best || q.bytes > best->bytes)) best = &q;
+        if (!best) {
+            out.emplace_back();
+            best = &out.back();
+        }
+        best->who.push_back(m.second);
+        best->bytes -= m.first;
+    }
+    if (!large.who.empty()) out.push_back(large);
+    return out;
+}
+
+// Time of a step of tiled members or of one untiled group, from what the
+// headline solve and the groups above measured per plane of a tile and per
+// block (at 256 compute units), with their launches.
+static double tiled_us(int mode, const std::vector<lbm3d_solver*>& members, int tz, int by, int cus)
+{
+    std::vector<Grid> grids;
+    bool layers = false;
+    for (const lbm3d_solver* h : members) {
+        grids.push_back(h->g);
+        layers = layers || ghost_faces(h->g, h->bc, true) != 0;
+    }
+    return tile_makespan(grids, by, plan_depth(mode, tz, grids, by, cus), cus) * (mode == LBM3D_FP64 ? 3.3 : 3.1) +
+           (layers ? 9.0 : 3.0);
+}
+static double blocks_us(int mode, const std::vector<lbm3d_solver*>& members, const GroupMembers& part, int cus)
+{
+    double blocks = 0.0;
+    for (int32_t k : part.who) blocks += block_grid(members[(size_t)k]->g).count;
+    return 2.5 + blocks * (mode == LBM3D_FP64 ? 0.017 : 0.007) * 256.0 / cus;
+}
+
+// The groups of a plan: as group_members has them, or all members tiled.
+static std::vector<GroupMembers> plan_groups(const std::vector<lbm3d_solver*>& members, int tz, int by, int cus)
+{
+    std::vector<GroupMembers> parts = group_members(members);
+    const int mode = members[0]->mode;
+    double apart = 0.0;
+    for (const GroupMembers& part : parts) {
+        std::vector<lbm3d_solver*> mine;
+        for (int32_t k : part.who) mine.push_back(members[(size_t)k]);
+        apart += part.tiled ? tiled_us(mode, mine, tz, by, cus) : blocks_us(mode, members, part, cus);
+    }
+    if (apart <= tiled_us(mode, members, tz, by, cus)) return parts;
+    GroupMembers all;
+    all.tiled = true;
+    for (size_t k = 0; k < members.size(); k++) all.who.push_back((int32_t)k);
+    return {all};
+}
+
+// layer jobs of tiled members (faces the tiles leave to memory)
+static void layer_jobs(const std::vector<lbm3d_solver*>& members, std::vector<BatchLayerJob>& ljobs,
+                       std::vector<int32_t>& block_job, int& nlblocks)
+{
     ljobs.clear();
     nlblocks = 0;
     for (size_t k = 0; k < members.size(); k++) {
         const Grid& g = members[k]->g;
         const uint32_t faces = ghost_faces(g, members[k]->bc, true);
-        rest[k] = faces;
         if (!faces) continue;
         int64_t lines = 0;
         for (int face = 0; face < 6; face++) {
@@ -216,9 +337,9 @@ static void layer_jobs(const std::vector<lbm3d_solver*>& members, std::vector<ui
 static size_t tables_need(size_t nmembers, size_t ntiles, size_t nljobs, size_t nlblocks)
 {
     return align256(nmembers * sizeof(BatchSolve)) + align256(ntiles * sizeof(BatchTile)) +
-           align256(sizeof(BatchQueue)) + align256(nljobs * sizeof(BatchLayerJob)) +
-           align256(nlblocks * sizeof(int32_t)) + align256(nmembers * sizeof(BatchCount)) +
-           nmembers * sizeof(uint32_t) + 256;
+           align256(9 * sizeof(int32_t) + BATCH_MAX_LISTS * sizeof(uint32_t)) +
+           align256(nljobs * sizeof(BatchLayerJob)) + align256(nlblocks * sizeof(int32_t)) +
+           align256(nmembers * sizeof(BatchCount)) + nmembers * sizeof(uint32_t) + 256;
 }
 
 size_t BatchPlan::table_bytes(const std::vector<lbm3d_solver*>& members, int tz)
@@ -231,43 +352,151 @@ size_t BatchPlan::table_bytes(const std::vector<lbm3d_solver*>& members, int tz)
     TilePlan p;
     const int cus = device_cus();
     if (plan_tiles(grids, by, plan_depth(mode, tz, grids, by, cus), cus, p) != LBM3D_OK) return (size_t)-1;
-    std::vector<uint32_t> rest;
     std::vector<BatchLayerJob> lj;
     std::vector<int32_t> bj;
     int nlb = 0;
-    layer_jobs(members, rest, lj, bj, nlb);
+    layer_jobs(members, lj, bj, nlb);
     return tables_need(members.size(), p.tiles.size(), lj.size(), (size_t)nlb);
 }
 
 int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t s, int tz, void* dev, size_t cap)
 {
-    // work still queued may read the old tables or replay the old graph
+    // work still queued may read the old tables or replay the old graphs
     if (last_stream_ && hipStreamSynchronize(last_stream_) != hipSuccess) return LBM3D_E_DEVICE;
     last_stream_ = nullptr;
-    release_graph();
-    members_ = members;
-    plan_ = TilePlan();
-    hcount_.assign(members.size(), BatchCount{0, 0});
+    release_graphs();
+    members_.clear();
+    order_.clear();
     count_pending_ = false;
     if (members.empty()) return LBM3D_OK;
     mode_ = members[0]->mode;
     by_ = mode_ == LBM3D_FP64 ? 4 : 8;
-    // plain stores when the members' levels together fit the memory-side
-    // cache, as for a single solve
-    int64_t level_bytes = 0;
-    for (lbm3d_solver* h : members) level_bytes += 2 * (int64_t)f_bytes(h->g, h->mode);
-    stream_ = level_bytes > STREAM_MIN_BYTES;
-    std::vector<Grid> grids;
-    for (lbm3d_solver* h : members) grids.push_back(h->g);
     const int cus = device_cus();
-    tz_ = plan_depth(mode_, tz, grids, by_, cus);
-    int32_t rc = plan_tiles(grids, by_, tz_, cus, plan_);
-    if (rc) return rc;
 
-    std::vector<BatchSolve> table(members.size());
-    for (size_t k = 0; k < members.size(); k++) {
-        lbm3d_solver* h = members[k];
-        BatchSolve& d = table[k];
+    // The tables, laid out in a host image of the device memory: the solves
+    // in group order and the members' health words, then per group its
+    // queue, counts and work items (with the solves' indices in the group).
+    std::vector<char> image;
+    auto place = [&](size_t bytes) {
+        const size_t at = align256(image.size());
+        image.resize(at + bytes, 0);
+        return at;
+    };
+    const std::vector<GroupMembers> parts = plan_groups(members, tz, by_, cus);
+    const size_t solves_at = place(members.size() * sizeof(BatchSolve));
+    const size_t health_at = place(members.size() * sizeof(uint32_t));
+    struct Offsets {
+        size_t queue, counts, items, grids, layers, blockjob;
+    };
+    std::vector<Offsets> offs;
+    for (const GroupMembers& part : parts) {
+        Group q;
+        q.first = (int)members_.size();
+        q.n = (int)part.who.size();
+        q.tiled = part.tiled;
+        std::vector<lbm3d_solver*> mine;
+        for (int32_t k : part.who) {
+            members_.push_back(members[(size_t)k]);
+            order_.push_back(k);
+            mine.push_back(members[(size_t)k]);
+        }
+        Offsets o{};
+        o.queue = place(sizeof(BatchQueue));
+        o.counts = place(2 * mine.size() * sizeof(BatchCount));
+        std::vector<BatchTile> items;
+        if (part.tiled) {
+            std::vector<Grid> grids;
+            int64_t level_bytes = 0;
+            for (lbm3d_solver* h : mine) {
+                grids.push_back(h->g);
+                level_bytes += 2 * (int64_t)f_bytes(h->g, h->mode);
+            }
+            // plain stores when the levels together fit the memory-side
+            // cache, as for a single solve
+            q.stream = level_bytes > STREAM_MIN_BYTES;
+            TilePlan plan;
+            int32_t rc = plan_tiles(grids, by_, plan_depth(mode_, tz, grids, by_, cus), cus, plan);
+            if (rc) {
+                release_graphs();
+                members_.clear();
+                return rc;
+            }
+            items.swap(plan.tiles);
+            q.nlists = plan.nlists;
+            q.nblocks = plan.nblocks;
+            std::memcpy(image.data() + o.queue, &plan.queue, sizeof(BatchQueue));
+            std::vector<BatchLayerJob> ljobs;
+            std::vector<int32_t> block_job;
+            layer_jobs(mine, ljobs, block_job, q.nlblocks);
+            if (q.nlblocks) {
+                o.layers = place(ljobs.size() * sizeof(BatchLayerJob));
+                std::memcpy(image.data() + o.layers, ljobs.data(), ljobs.size() * sizeof(BatchLayerJob));
+                o.blockjob = place(block_job.size() * sizeof(int32_t));
+                std::memcpy(image.data() + o.blockjob, block_job.data(), block_job.size() * sizeof(int32_t));
+            }
+        } else {
+            o.grids = place(mine.size() * sizeof(BlockGrid));
+            for (size_t k = 0; k < mine.size(); k++) {
+                const BlockGrid bg = block_grid(mine[k]->g);
+                std::memcpy(image.data() + o.grids + k * sizeof(BlockGrid), &bg, sizeof(BlockGrid));
+                const int first = q.nblocks;
+                for (uint32_t b = 0; b < bg.count; b += BATCH_BLOCKS) {
+                    items.push_back(BatchTile{(int32_t)k, 0, 0, first, 0});
+                    q.nblocks += BATCH_BLOCKS;
+                }
+            }
+        }
+        o.items = place(items.size() * sizeof(BatchTile));
+        std::memcpy(image.data() + o.items, items.data(), items.size() * sizeof(BatchTile));
+        groups_.push_back(q);
+        offs.push_back(o);
+    }
+    const size_t need = image.size();
+    char* base = (char*)dev;
+    if (dev) {
+        if (need > cap) {
+            release_graphs();
+            members_.clear();
+            return LBM3D_E_NOMEM;
+        }
+        if (dmem_) (void)hipFree(dmem_);
+        dmem_ = nullptr;
+        dbytes_ = 0;
+    } else {
+        if (need > dbytes_) {
+            if (dmem_) (void)hipFree(dmem_);
+            dmem_ = nullptr;
+            dbytes_ = 0;
+            hipError_t e = hipMalloc(&dmem_, need);
+            if (e != hipSuccess) {
+                release_graphs();
+                members_.clear();
+                return herr(e);
+            }
+            dbytes_ = need;
+        }
+        base = (char*)dmem_;
+    }
+    dsolves_ = (BatchSolve*)(base + solves_at);
+    dhealth_ = (uint32_t*)(base + health_at);
+    for (size_t j = 0; j < groups_.size(); j++) {
+        Group& q = groups_[j];
+        const Offsets& o = offs[j];
+        q.queue = (BatchQueue*)(base + o.queue);
+        q.counts = (BatchCount*)(base + o.counts);
+        q.items = (BatchTile*)(base + o.items);
+        q.layers = (BatchLayerJob*)(base + o.layers);
+        q.blockjob = (int32_t*)(base + o.blockjob);
+        BatchQueue hq;
+        std::memcpy(&hq, image.data() + o.queue, sizeof(hq));
+        hq.blocks = (const BlockGrid*)(base + o.grids);
+        hq.counts = q.counts;
+        hq.members = q.n;
+        std::memcpy(image.data() + o.queue, &hq, sizeof(hq));
+    }
+    for (size_t k = 0; k < members_.size(); k++) {
+        const lbm3d_solver* h = members_[k];
+        BatchSolve d;
         std::memset(&d, 0, sizeof(d));
         d.g = h->g;
         d.bc = h->bc;
@@ -278,61 +507,22 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         d.health = h->health;
         d.md = h->md;
         d.mf = h->mf;
+        std::memcpy(image.data() + solves_at + k * sizeof(BatchSolve), &d, sizeof(d));
     }
-    std::vector<BatchLayerJob> ljobs;
-    std::vector<int32_t> block_job;
-    layer_jobs(members, ghost_rest_, ljobs, block_job, nlblocks_);
-    nljobs_ = (int)ljobs.size();
-
-    const size_t sb = table.size() * sizeof(BatchSolve);
-    const size_t tb = plan_.tiles.size() * sizeof(BatchTile);
-    const size_t lb = ljobs.size() * sizeof(BatchLayerJob);
-    const size_t bb = block_job.size() * sizeof(int32_t);
-    const size_t need = tables_need(table.size(), plan_.tiles.size(), ljobs.size(), block_job.size());
-    char* base = nullptr;
-    if (dev) {
-        if (need > cap) return LBM3D_E_NOMEM;
-        if (dmem_) {
-            (void)hipFree(dmem_);
-            dmem_ = nullptr;
-            dbytes_ = 0;
-        }
-        base = (char*)dev;
-    } else {
-        if (need > dbytes_) {
-            if (dmem_) (void)hipFree(dmem_);
-            dmem_ = nullptr;
-            dbytes_ = 0;
-            hipError_t e = hipMalloc(&dmem_, need);
-            if (e != hipSuccess) return herr(e);
-            dbytes_ = need;
-        }
-        base = (char*)dmem_;
-    }
-    dsolves_ = (BatchSolve*)base;
-    dtiles_ = (BatchTile*)(base + align256(sb));
-    dqueue_ = (BatchQueue*)((char*)dtiles_ + align256(tb));
-    dlayers_ = (BatchLayerJob*)((char*)dqueue_ + align256(sizeof(BatchQueue)));
-    dblockjob_ = (int32_t*)((char*)dlayers_ + align256(lb));
-    const size_t cb = hcount_.size() * sizeof(BatchCount);
-    dcount_ = (BatchCount*)((char*)dblockjob_ + align256(bb));
-    dhealth_ = (uint32_t*)((char*)dcount_ + align256(cb));
+    hcount_.assign(members_.size(), BatchCount{0, 0});
     // the tiles read some layers from memory, which members that last
-    // stepped alone and untiled have left behind
+    // stepped untiled have left behind
     hipError_t e = hipSuccess;
-    for (size_t k = 0; k < members.size() && e == hipSuccess; k++) {
-        lbm3d_solver* h = members[k];
-        if (!h->layers_stale) continue;
-        e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[h->cur], s, ghost_rest_[k]);
-        if (e == hipSuccess) h->layers_stale = false;
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(dsolves_, table.data(), sb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dtiles_, plan_.tiles.data(), tb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dqueue_, &plan_.queue, sizeof(BatchQueue), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && lb) e = hipMemcpyAsync(dlayers_, ljobs.data(), lb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && bb) e = hipMemcpyAsync(dblockjob_, block_job.data(), bb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dcount_, hcount_.data(), cb, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // host tables die at return
+    for (const Group& q : groups_)
+        for (int k = q.first; q.tiled && k < q.first + q.n && e == hipSuccess; k++) {
+            lbm3d_solver* h = members_[(size_t)k];
+            if (!h->layers_stale) continue;
+            e = launch_ghosts(h->mode, h->g, h->bc, h->md, h->p.inflow, false, h->f[h->cur], s,
+                              ghost_faces(h->g, h->bc, true));
+            if (e == hipSuccess) h->layers_stale = false;
+        }
+    if (e == hipSuccess) e = hipMemcpyAsync(base, image.data(), need, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host image dies at return
     last_stream_ = nullptr;
     return herr(e);
 }
@@ -341,29 +531,35 @@ int32_t BatchPlan::health(std::vector<uint32_t>& out, hipStream_t s)
 {
     out.assign(members_.size(), 0u);
     if (members_.empty()) return LBM3D_OK;
+    std::vector<uint32_t> got(members_.size(), 0u);
     hipError_t e = launch_gather_health(dsolves_, (int)members_.size(), dhealth_, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(out.data(), dhealth_, out.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(got.data(), dhealth_, got.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess && s == last_stream_) count_pending_ = false;
+    for (size_t k = 0; k < got.size(); k++) out[(size_t)order_[k]] = got[k];
     return herr(e);
 }
 
 hipError_t BatchPlan::launch_at(int parity, hipStream_t s)
 {
     last_stream_ = s;
-    return enqueue(parity & 1, s);
+    hipError_t e = hipSuccess;
+    for (const Group& q : groups_)
+        if (e == hipSuccess) e = enqueue(q, parity & 1, s);
+    return e;
 }
 
-hipError_t BatchPlan::enqueue(int parity, hipStream_t s)
+hipError_t BatchPlan::enqueue(const Group& q, int parity, hipStream_t s)
 {
-    hipError_t e = launch_batch_step(mode_, by_, stream_, dsolves_, dtiles_, dqueue_, plan_.nlists, plan_.nblocks,
-                                     parity, dcount_, s);
-    if (e != hipSuccess) return e;
+    const BatchCount* counts = q.counts + (parity == -2 ? q.n : 0);
+    const BatchSolve* solves = dsolves_ + q.first;
+    hipError_t e = launch_batch_step(mode_, q.tiled ? by_ : 0, q.stream, solves, q.items, q.queue, q.nlists, q.nblocks,
+                                     parity, counts, s);
     // boundary layers the tiles do not form themselves, all members at once
-    e = launch_batch_layers(mode_, dsolves_, dlayers_, dblockjob_, nlblocks_, parity, dcount_, s);
-    if (e != hipSuccess || parity >= 0) return e;
-    return launch_batch_count(dcount_, (int)members_.size(), s);
+    if (e == hipSuccess && q.nlblocks)
+        e = launch_batch_layers(mode_, solves, q.layers, q.blockjob, q.nlblocks, parity, counts, s);
+    return e;
 }
 
 int32_t BatchPlan::run(int64_t k, hipStream_t s, bool graphs, const std::vector<int64_t>* limit)
@@ -391,54 +587,61 @@ int32_t BatchPlan::run(int64_t k, hipStream_t s, bool graphs, const std::vector<
     // (so it never grows), target = done + the member's steps
     std::vector<int64_t> steps(members_.size(), k);
     for (size_t m = 0; m < members_.size(); m++) {
-        if (limit) steps[m] = std::max<int64_t>(0, std::min<int64_t>(k, (*limit)[m]));
+        if (limit) steps[m] = std::max<int64_t>(0, std::min<int64_t>(k, (*limit)[(size_t)order_[m]]));
         hcount_[m].done &= 1;
         hcount_[m].target = hcount_[m].done + (int32_t)steps[m];
     }
-    hipError_t e = hipMemcpyAsync(dcount_, hcount_.data(), hcount_.size() * sizeof(BatchCount),
-                                  hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return herr(e);
-    count_pending_ = true;
-    int64_t left = k;
-    // the launches carry nothing step-specific (each member's parity comes
-    // from its count), so one captured run of BATCH_GRAPH_STEPS serves all
-    while (graphs && left >= BATCH_GRAPH_STEPS) {
-        if (!graph_) {
-            if (!capture_stream_) {
-                e = hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking);
+    for (Group& q : groups_) {
+        int64_t left = 0;
+        for (int m = q.first; m < q.first + q.n; m++) left = std::max(left, steps[(size_t)m]);
+        if (left == 0) continue;
+        hipError_t e = hipMemcpyAsync(q.counts, hcount_.data() + q.first, (size_t)q.n * sizeof(BatchCount),
+                                      hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return herr(e);
+        count_pending_ = true;
+        // the launches carry nothing step-specific but which copy of the
+        // counts they read (each member's parity comes from its count), so
+        // one captured run of BATCH_GRAPH_STEPS, an even number, serves all
+        while (graphs && left >= BATCH_GRAPH_STEPS) {
+            if (!q.graph) {
+                if (!capture_stream_) {
+                    e = hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking);
+                    if (e != hipSuccess) return herr(e);
+                }
+                hipGraph_t graph = nullptr;
+                e = hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal);
+                if (e != hipSuccess) return herr(e);
+                for (int j = 0; j < BATCH_GRAPH_STEPS && e == hipSuccess; j++)
+                    e = enqueue(q, -1 - (j & 1), capture_stream_);
+                hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
+                if (e != hipSuccess || e2 != hipSuccess) {
+                    if (graph) (void)hipGraphDestroy(graph);
+                    return herr(e != hipSuccess ? e : e2);
+                }
+                e = hipGraphInstantiate(&q.graph, graph, nullptr, nullptr, 0);
+                (void)hipGraphDestroy(graph);
                 if (e != hipSuccess) return herr(e);
             }
-            hipGraph_t graph = nullptr;
-            e = hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal);
+            e = hipGraphLaunch(q.graph, s);
             if (e != hipSuccess) return herr(e);
-            for (int j = 0; j < BATCH_GRAPH_STEPS && e == hipSuccess; j++) e = enqueue(-1, capture_stream_);
-            hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
-            if (e != hipSuccess || e2 != hipSuccess) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return herr(e != hipSuccess ? e : e2);
-            }
-            e = hipGraphInstantiate(&graph_, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
+            left -= BATCH_GRAPH_STEPS;
+        }
+        for (int j = 0; j < left; j++) {
+            e = enqueue(q, -1 - (j & 1), s);
             if (e != hipSuccess) return herr(e);
         }
-        e = hipGraphLaunch(graph_, s);
-        if (e != hipSuccess) return herr(e);
-        left -= BATCH_GRAPH_STEPS;
-    }
-    for (; left > 0; left--) {
-        e = enqueue(-1, s);
-        if (e != hipSuccess) return herr(e);
-    }
-    // members advance by their steps; their current buffer flips with an
-    // odd count (the device table keeps the build-time buffers, and each
-    // count's done its parity since build)
-    for (size_t m = 0; m < members_.size(); m++) {
-        lbm3d_solver* h = members_[m];
-        const int64_t n = steps[m];
-        hcount_[m].done = (hcount_[m].done + (int32_t)(n & 1)) & 1;
-        if (n == 0) continue;
-        h->steps += n;
-        if (n & 1) h->cur ^= 1;
+        // members advance by their steps; their current buffer flips with
+        // an odd count (the device table keeps the build-time buffers, and
+        // each count's done its parity since build)
+        for (int m = q.first; m < q.first + q.n; m++) {
+            lbm3d_solver* h = members_[(size_t)m];
+            const int64_t n = steps[(size_t)m];
+            hcount_[(size_t)m].done = (hcount_[(size_t)m].done + (int32_t)(n & 1)) & 1;
+            if (n == 0) continue;
+            h->steps += n;
+            if (n & 1) h->cur ^= 1;
+            if (!q.tiled) h->layers_stale = true;
+        }
     }
     return LBM3D_OK;
 }
@@ -508,8 +711,13 @@ extern "C" int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* n
 // per device, held until the process ends.  In host code its name is only a
 // stand-in: the device address of each device's copy comes from
 // hipGetSymbolAddress and is kept per device.
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)4 << 20;
-static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
+// A batch is taken if its tables with every member tiled in one group fit
+// NOALLOC_SCRATCH_BYTES; the array holds a margin above that for what the
+// groups need beyond it (a second copy of the counts, a block grid and an
+// entry per untiled member and 16 K nodes, and up to 2 KB of alignment per
+// group, of which there are at most as many as 96 MiB go into the device).
+constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)4 << 20, NOALLOC_MARGIN = (size_t)12 << 20;
+static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES + NOALLOC_MARGIN];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -550,7 +758,7 @@ extern "C" int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const in
     for (int32_t k = 1; k < count; k++)
         if (hs[k]->stream != s && hipStreamSynchronize(hs[k]->stream) != hipSuccess) return LBM3D_E_DEVICE;
     BatchPlan plan;  // tables in the scratch array, steps launched directly (no graph)
-    return batch_advance(hs, count, nsteps, s, plan, ptr, NOALLOC_SCRATCH_BYTES, false);
+    return batch_advance(hs, count, nsteps, s, plan, ptr, NOALLOC_SCRATCH_BYTES + NOALLOC_MARGIN, false);
 }
 
 extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus,

@@ -24,9 +24,10 @@ struct TilePlan {
 // list runs its deepest tiles first.  Host only.
 int32_t plan_tiles(const std::vector<Grid>& grids, int by, int tz, int cus, TilePlan& out);
 
-// A fixed set of solves (one precision) advanced together: a device table
-// of the solves, the tile lists over all of them and a persistent launch
-// per step; runs of steps are replayed from a captured graph.
+// A fixed set of solves (one precision) advanced together, group by group
+// (see group_members): a device table of the solves, the work items of each
+// group and one launch per step and group (and one for the boundary layers
+// tiles leave to memory); runs of steps are replayed from captured graphs.
 class BatchPlan {
 public:
     BatchPlan() = default;
@@ -59,32 +60,34 @@ public:
     // Health words of the members (in build order) after the work queued
     // on `s`; waits for `s`.
     int32_t health(std::vector<uint32_t>& out, hipStream_t s);
-    int ntiles() const { return (int)plan_.tiles.size(); }
-    int by() const { return by_; }
-    int tz() const { return tz_; }
+    bool empty() const { return members_.empty(); }
 
 private:
-    hipError_t enqueue(int parity, hipStream_t s);  // parity < 0: by the members' counts
-    void release_graph();
+    struct Group {
+        int first = 0, n = 0;  // its members in members_
+        bool tiled = false;    // stepped by the tiled kernel, else by the untiled one
+        bool stream = false;   // non-temporal stores (tiled, levels beyond STREAM_MIN_BYTES)
+        int nlists = 0, nblocks = 0, nlblocks = 0;
+        BatchQueue* queue = nullptr;      // (device)
+        BatchCount* counts = nullptr;     // step counts in the current run, two copies
+        BatchTile* items = nullptr;       // tiles, or entries of blocks
+        BatchLayerJob* layers = nullptr;  // boundary-layer jobs (sorted by first workgroup)
+        int32_t* blockjob = nullptr;      // job of each boundary-layer workgroup
+        hipGraphExec_t graph = nullptr;
+    };
+    hipError_t enqueue(const Group& q, int parity, hipStream_t s);  // parity < 0: by the counts (-1, -2: which copy)
+    void release_graphs();
 
-    std::vector<lbm3d_solver*> members_;
-    int mode_ = 0, by_ = 8, tz_ = 8;
-    bool stream_ = true;  // non-temporal stores (the members' levels exceed STREAM_MIN_BYTES)
-    TilePlan plan_;
+    std::vector<lbm3d_solver*> members_;  // group by group
+    std::vector<int32_t> order_;          // their places in the caller's list
+    std::vector<Group> groups_;
+    int mode_ = 0, by_ = 8;
     void* dmem_ = nullptr;  // tables allocated by the plan (nullptr with a caller's buffer)
     size_t dbytes_ = 0;
     BatchSolve* dsolves_ = nullptr;
-    BatchTile* dtiles_ = nullptr;
-    BatchQueue* dqueue_ = nullptr;
-    BatchLayerJob* dlayers_ = nullptr;  // boundary-layer jobs (sorted by first workgroup)
-    int32_t* dblockjob_ = nullptr;      // job of each boundary-layer workgroup
-    uint32_t* dhealth_ = nullptr;       // gathered health words, one per member
-    BatchCount* dcount_ = nullptr;      // step counts of the members in the current run
-    std::vector<BatchCount> hcount_;    // their host copy (source of the upload; done = parity since build)
-    bool count_pending_ = false;        // hcount_ was uploaded and the stream not waited for since
-    int nljobs_ = 0, nlblocks_ = 0;
-    std::vector<uint32_t> ghost_rest_;  // per member: faces left to the boundary-layer launch
-    hipGraphExec_t graph_ = nullptr;
+    uint32_t* dhealth_ = nullptr;     // gathered health words, one per member
+    std::vector<BatchCount> hcount_;  // host copy of the counts (source of the upload; done = parity since build)
+    bool count_pending_ = false;      // hcount_ was uploaded and the stream not waited for since
     hipStream_t capture_stream_ = nullptr;
     hipStream_t last_stream_ = nullptr;  // stream of the last enqueued work (drained before teardown)
 };

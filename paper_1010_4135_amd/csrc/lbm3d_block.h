@@ -35,8 +35,6 @@
 
 namespace lbm3d {
 
-// A block: BLOCK_X x BLOCK_Y nodes, one per thread.
-constexpr int BLOCK_T = 256, BLOCK_X = 32, BLOCK_Y = BLOCK_T / BLOCK_X;
 // BX x BY nodes of one plane in LDS, all 15 velocities, with the halo the x and y
 // stencils reach: two rows (BX wide) and two columns (BY tall) beyond each
 // side.  Per velocity the rows -2 .. BY + 1 come first, one after the other
@@ -58,17 +56,7 @@ struct BlockPlane {
     }
 };
 
-// floor(2^32 / d) (2^32 - 1 for d = 1)
-inline uint32_t div_magic(uint32_t d) { return d <= 1 ? 0xffffffffu : (uint32_t)(((uint64_t)1 << 32) / d); }
-
-// Blocks of a level, numbered strip by strip: a strip is `ys` block rows of
-// every plane (the last one what is left), its blocks numbered x fastest,
-// then y, then z.
-struct BlockGrid {
-    uint32_t ntx, ys, strip, full, last;  // blocks: per row, rows of a strip, per strip, strips of ys rows, rows left
-    uint32_t xmagic, smagic, pmagic, lmagic;
-};
-// a / d and a % d for d with magic = div_magic(d): the product's high word
+// a / d and a % d for d with magic = floor(2^32 / d): the product's high word
 // is the quotient or one less.
 __device__ __forceinline__ uint32_t div_rem(uint32_t a, uint32_t d, uint32_t magic, uint32_t& rem)
 {
@@ -128,168 +116,149 @@ __device__ __forceinline__ Macro<M> pick_macro(bool first, const Macro<M>& a, co
     return q;
 }
 
-// Arguments of the kernel.  Held in scalar registers from the first use to
-// the last they would overflow the scalar file (the model constants alone
-// are 40 dwords in double) and be spilled into vector lanes; `again` reads
-// them once more from the argument segment (the scalar cache) instead.
-template <int MODE>
+// What the step of a solve is described by: the kernel's argument segment
+// (BlockArgs), or the solve's entry in a batch's table (BatchSolve).  Held in
+// scalar registers from the first use to the last, this would overflow the
+// scalar file (the model constants alone are 40 dwords in double) and be
+// spilled into vector lanes; `again` makes later uses read it once more,
+// through the scalar cache, instead.
 struct BlockArgs {
-    StepArgs<MODE> A;
-    BlockGrid bg;
+    Grid g;
+    FaceBC bc;
+    double xin[2][5];
     Model<double> md;
     Model<float> mf;
+    BlockGrid bg;
+    const void* f;
+    void* fn;
+    uint32_t* health;
 };
-template <int MODE>
-__device__ __forceinline__ const BlockArgs<MODE>& again()
+template <typename D>
+__device__ __forceinline__ const D& again(uint64_t at)
 {
-    using AP = const __attribute__((address_space(4))) BlockArgs<MODE>*;
-    uint64_t v = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
-    asm volatile("" : "+s"(v));
-    return *(const BlockArgs<MODE>*)reinterpret_cast<AP>(v);
+    using AP = const __attribute__((address_space(4))) D*;
+    asm volatile("" : "+s"(at));
+    return *(const D*)reinterpret_cast<AP>(at);
 }
 
 __device__ __forceinline__ constexpr bool formed(int kind) { return kind == BC_OUTFLOW || kind == BC_REFLECT; }
 
-// Boundary layers of the x and y faces a block's stencils reach, in its LDS
-// plane.  xr, yr: columns and rows from the block's first to the high faces.
-// A wavefront that holds both nodes next to a face forms the layers, which
-// only it reads, from its lanes' moments:
-//  - x: its RPW rows, one value per lane (row, layer, velocity);
-//  - y: its columns, one (column, layer) per lane.
-// Where the pair is split between wavefronts or blocks, or the fixed x
-// layers are out of reach in memory (xmem false), one thread per (line,
-// layer) forms them from the staged values, and a barrier follows.
-template <int MODE>
-__device__ __forceinline__ void block_layers(BlockPlane<typename Types<MODE>::S>& P, int x0, int y0, bool xmem,
+// Moments of a block's nodes next to its x and y faces, by face side, the
+// node's distance from the face (0, 1) and line.
+template <typename M>
+struct FaceNodes {
+    Macro<M> x[2][2][BLOCK_Y], y[2][2][BLOCK_X];
+};
+
+// Boundary layers of the x and y faces a block's stencils reach, formed in
+// its LDS plane: the threads of the nodes next to a face leave their moments
+// in Q, then one thread per (line, layer) forms a layer node, a wavefront
+// for each y face and one for the x faces.  (Each wavefront forming the x
+// layers of its own rows instead, without these barriers, costs every
+// wavefront of the block the 150 instructions: an extrapolating x face then
+// adds 1.7 us to a 64^3 step instead of 1.4.)  Of a pair of nodes split between two
+// blocks the other block's node is in this one's halo, from which its
+// moments are computed.  The fixed x layers are formed here too where they
+// are out of reach in memory (xmem false).
+template <int MODE, typename D>
+__device__ __forceinline__ void block_layers(const D& K, BlockPlane<typename Types<MODE>::S>& P,
+                                             FaceNodes<typename Types<MODE>::M>& Q, int x0, int y0, bool xmem,
                                              const Macro<typename Types<MODE>::M>& mac)
 {
     using S = typename Types<MODE>::S;
     using C = typename Types<MODE>::C;
     using M = typename Types<MODE>::M;
     using Plane = BlockPlane<S>;
-    constexpr int BX = Plane::BX, BY = Plane::BY, RPW = 64 / BX;
-    const BlockArgs<MODE>& K = again<MODE>();
+    constexpr int BX = Plane::BX, BY = Plane::BY;
+    static_assert(2 * BX == 64 && 4 * BY <= 64 && BLOCK_T == 256, "a wavefront per y face, one for both x faces");
     const Model<C>& mc = pick<C>(K.md, K.mf);
     const Model<M>& mm = pick<M>(K.md, K.mf);
-    const int kx0 = K.A.bc.kind[0], kx1 = K.A.bc.kind[1], ky0 = K.A.bc.kind[2], ky1 = K.A.bc.kind[3];
-    const int xr = K.A.g.nx - x0, yr = K.A.g.ny - y0;
-    const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int wrow = __builtin_amdgcn_readfirstlane(tid / 64) * RPW;  // first row of this wavefront
-    const bool splitx = xr == 1 || xr == BX + 1;
-    const bool splity = yr == 1 || yr == BY + 1 || (yr - 1) / RPW != (yr - 2) / RPW;
-#pragma unroll 1
-    for (int side = 0; side < 2; side++) {
-        const int kind = side ? kx1 : kx0;
-        if (!formed(kind) || !(side ? xr <= BX && !splitx : x0 == 0)) continue;
-        const int a = side ? xr - 1 : 0, d = side ? 1 : -1;  // the node next to the face, outwards
-#pragma unroll
-        for (int p = 0; p < RPW / 2; p++) {
-            const int r2 = lane >= 30 ? 1 : 0, l2 = lane - 30 * r2;
-            const int j = l2 >= NV ? 1 : 0, iv = min(l2 - NV * j, NV - 1);
-            const int r = 2 * p + r2;
-            const Macro<M> q0 = shfl_macro(mac, r * BX + a);
-            Macro<M> q1 = shfl_macro(mac, r * BX + a - d);
-            q1 = pick_macro(kind == BC_REFLECT, q0, q1);
-            M c, m;
-            layer_coefs(kind, j + 1, c, m);
-            const C val = static_cast<C>(feq_vel<M>(iv, eq_coef<M, M>(layer_state(q0, q1, c, m, 0), mm), mm));
-            if (lane < 60) P.v[iv][Plane::at(a + (j + 1) * d, wrow + r)] = static_cast<S>(val);
-        }
-    }
-#pragma unroll 1
-    for (int side = 0; side < 2; side++) {
-        const int kind = side ? ky1 : ky0;
-        if (!formed(kind) || !(side ? yr <= BY && !splity : y0 == 0)) continue;
-        const int a = side ? yr - 1 : 0, d = side ? 1 : -1;
-        if (a / RPW * RPW != wrow) continue;
-        const int j = lane / BX, col = lane % BX;
-        const Macro<M> q0 = shfl_macro(mac, (a - wrow) * BX + col);
-        Macro<M> q1 = shfl_macro(mac, (a - d - wrow) * BX + col);
-        q1 = pick_macro(kind == BC_REFLECT, q0, q1);
-        M c, m;
-        layer_coefs(kind, j + 1, c, m);
-        C lf[NV];
-        equilibrium<C, M>(layer_state(q0, q1, c, m, 1), mm, mc, lf);
-        if (j < 2) {
-            const int pt = Plane::at(col, a + (j + 1) * d);
-#pragma unroll
-            for (int i = 0; i < NV; i++) P.v[i][pt] = static_cast<S>(lf[i]);
-        }
-    }
-    const bool jx0 = x0 == 0 && kx0 == BC_INFLOW && !xmem;
-    const bool jx1 = xr <= BX + 1 && (formed(kx1) ? splitx : kx1 == BC_INFLOW && !xmem);
-    const bool jy1 = yr <= BY + 1 && formed(ky1) && splity;
-    if (!(jx0 || jx1 || jy1)) return;
-    const int n0 = jx0 ? 2 * BY : 0, n1 = n0 + (jx1 ? 2 * BY : 0), n2 = n1 + (jy1 ? 2 * BX : 0);
-    if (tid < n2) {
-        const int face = tid < n0 ? 0 : tid < n1 ? 1 : 3;
-        const int k = tid - (face == 0 ? 0 : face == 1 ? n0 : n1);
-        const bool isx = face < 2, high = face != 0;
-        const int len = isx ? BY : BX;
+    const int kx0 = K.bc.kind[0], kx1 = K.bc.kind[1], ky0 = K.bc.kind[2], ky1 = K.bc.kind[3];
+    // columns and rows from the block's first to the high faces
+    const int xr = K.g.nx - x0, yr = K.g.ny - y0;
+    const int tid = (int)threadIdx.x, tx = tid % BX, ty = tid / BX;
+    const bool fx0 = x0 == 0, fx1 = xr <= BX + 1, fy0 = y0 == 0, fy1 = yr <= BY + 1;
+    if (fx0 && tx < 2) Q.x[0][tx][ty] = mac;
+    if (fx1 && (unsigned)(xr - 1 - tx) < 2u) Q.x[1][xr - 1 - tx][ty] = mac;
+    if (fy0 && ty < 2) Q.y[0][ty][tx] = mac;
+    if (fy1 && (unsigned)(yr - 1 - ty) < 2u) Q.y[1][yr - 1 - ty][tx] = mac;
+    lds_barrier();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid & 63;
+    const bool isx = wave == 3;
+    const bool high = isx ? lane >= 2 * BY : wave == 1;
+    const int kind = isx ? (high ? kx1 : kx0) : (high ? ky1 : ky0);
+    const bool face = isx ? lane < 4 * BY && (high ? fx1 : fx0) : wave < 2 && (high ? fy1 : fy0);
+    if (face && (formed(kind) || (isx && kind == BC_INFLOW && !xmem))) {
+        const int k = isx ? lane % (2 * BY) : lane, len = isx ? BY : BX;
         const int layer = k >= len ? 2 : 1, line = k >= len ? k - len : k;
-        const int kind = face == 0 ? kx0 : face == 1 ? kx1 : ky1;
-        const int a = face == 0 ? 0 : face == 1 ? xr - 1 : yr - 1, d = high ? 1 : -1;
+        const int a = high ? (isx ? xr : yr) - 1 : 0, d = high ? 1 : -1;  // the node next to the face, outwards
         auto at = [&](int p) { return Plane::at(isx ? p : line, isx ? line : p); };
-        C b[NV];
-        const int pa = at(a), pb = at(a - d);
+        auto halo_node = [&](int p) {
+            C b[NV];
+            const int pp = at(p);
 #pragma unroll
-        for (int i = 0; i < NV; i++) b[i] = static_cast<C>(P.v[i][pa]);
-        const Macro<M> q0 = moments<M, C>(b, mm);
-#pragma unroll
-        for (int i = 0; i < NV; i++) b[i] = static_cast<C>(P.v[i][pb]);
-        const Macro<M> q1 = pick_macro(kind == BC_OUTFLOW, moments<M, C>(b, mm), q0);
+            for (int i = 0; i < NV; i++) b[i] = static_cast<C>(P.v[i][pp]);
+            return moments<M, C>(b, mm);
+        };
+        const Macro<M>* q = isx ? &Q.x[high ? 1 : 0][0][line] : &Q.y[high ? 1 : 0][0][line];
+        Macro<M> q0 = q[0], q1 = q[len];
+        const int size = isx ? BX : BY;
+        if (a == size) q0 = halo_node(a);
+        if (high && a == 0) q1 = halo_node(-1);
+        q1 = pick_macro(kind == BC_OUTFLOW, q1, q0);
         M c = M(0), m = M(1);
         if (kind != BC_INFLOW) layer_coefs(kind, layer, c, m);
-        Macro<M> q = layer_state(q0, q1, c, M(1), 2);
-        q.ux = isx ? m * q.ux : q.ux;
-        q.uy = isx ? q.uy : m * q.uy;
+        Macro<M> s = layer_state(q0, q1, c, M(1), 2);
+        s.ux = isx ? m * s.ux : s.ux;
+        s.uy = isx ? s.uy : m * s.uy;
         if (kind == BC_INFLOW) {
             // (selects: a per-lane index would put the argument in private
             // memory)
-            q.rho = static_cast<M>(high ? K.A.xin[1][0] : K.A.xin[0][0]);
-            q.ux = static_cast<M>(high ? K.A.xin[1][1] : K.A.xin[0][1]);
-            q.uy = static_cast<M>(high ? K.A.xin[1][2] : K.A.xin[0][2]);
-            q.uz = static_cast<M>(high ? K.A.xin[1][3] : K.A.xin[0][3]);
-            q.T = static_cast<M>(high ? K.A.xin[1][4] : K.A.xin[0][4]);
+            s.rho = static_cast<M>(high ? K.xin[1][0] : K.xin[0][0]);
+            s.ux = static_cast<M>(high ? K.xin[1][1] : K.xin[0][1]);
+            s.uy = static_cast<M>(high ? K.xin[1][2] : K.xin[0][2]);
+            s.uz = static_cast<M>(high ? K.xin[1][3] : K.xin[0][3]);
+            s.T = static_cast<M>(high ? K.xin[1][4] : K.xin[0][4]);
         }
         C lf[NV];
-        equilibrium<C, M>(q, mm, mc, lf);
+        equilibrium<C, M>(s, mm, mc, lf);
         const int to = a + layer * d;
-        if (to < (isx ? BX : BY) + 2) {  // (a block one short of the face reads its first layer only)
+        if (to < size + 2) {  // (a block one short of the face reads its first layer only)
             const int pt = at(to);
 #pragma unroll
             for (int i = 0; i < NV; i++) P.v[i][pt] = static_cast<S>(lf[i]);
         }
     }
-    lds_barrier();
 }
 
 // Layers of the z faces, formed by each thread for its own column into its
 // z neighbours (the plane is the block's own, so the branches are uniform).
-template <int MODE>
-__device__ __forceinline__ void block_z_layers(int z, const typename Types<MODE>::C (&f0)[NV],
+template <int MODE, typename D>
+__device__ __forceinline__ void block_z_layers(uint64_t args, int z, const typename Types<MODE>::C (&f0)[NV],
                                                typename Types<MODE>::C (&zm2)[NV], typename Types<MODE>::C (&zm1)[NV],
                                                typename Types<MODE>::C (&zp1)[NV], typename Types<MODE>::C (&zp2)[NV])
 {
     using C = typename Types<MODE>::C;
     using M = typename Types<MODE>::M;
-    const BlockArgs<MODE>& K = again<MODE>();
+    const D& K = again<D>(args);
     const Model<C>& mc = pick<C>(K.md, K.mf);
     const Model<M>& mm = pick<M>(K.md, K.mf);
     const Macro<M> mac = moments<M, C>(f0, mm);
 #pragma unroll 1
     for (int side = 0; side < 2; side++) {
-        const int kind = side ? K.A.bc.kind[5] : K.A.bc.kind[4];
-        const int d = side ? K.A.g.nz - 1 - z : z;
+        const int kind = side ? K.bc.kind[5] : K.bc.kind[4];
+        const int d = side ? K.g.nz - 1 - z : z;
         if (!formed(kind) || d > 1) continue;
         // the other node of the pair next to the face: one further in
         // (d = 0) or out (d = 1)
         const bool up = (side != 0) == (d != 0);
-        Macro<M> qm;
-        if (up)
-            qm = moments<M, C>(zp1, mm);
-        else
-            qm = moments<M, C>(zm1, mm);
+        Macro<M> qm = mac;
+        if (kind == BC_OUTFLOW || d == 1) {
+            if (up)
+                qm = moments<M, C>(zp1, mm);
+            else
+                qm = moments<M, C>(zm1, mm);
+        }
         const Macro<M> q0 = pick_macro(d == 0, mac, qm);
         const Macro<M> q1 = pick_macro(kind == BC_REFLECT, q0, pick_macro(d == 0, qm, mac));
         // layer 1: the first neighbour of the nodes next to the face, the
@@ -316,11 +285,13 @@ __device__ __forceinline__ void block_z_layers(int z, const typename Types<MODE>
     }
 }
 
-// PM: the level is in plane-major order.  U2: the second-order upwind
-// variant in place of NND.
-template <int MODE, bool U2, bool PM>
-__global__ void __launch_bounds__(BLOCK_T, MODE == MODE_FP64 ? 2 : 4)
-k_step_block(BlockArgs<MODE> args)
+// Block t of a solve: one step of its nodes from f to fn.  PM: the level is
+// in plane-major order.  U2: the second-order upwind variant in place of NND.
+template <int MODE, bool U2, bool PM, typename D>
+__device__ __forceinline__ void step_block(uint64_t args, const BlockGrid& bg, uint32_t t,
+                                           const typename Types<MODE>::S* __restrict__ f, typename Types<MODE>::S* fout,
+                                           BlockPlane<typename Types<MODE>::S>& P,
+                                           FaceNodes<typename Types<MODE>::M>& Q)
 {
     using S = typename Types<MODE>::S;
     using C = typename Types<MODE>::C;
@@ -328,23 +299,36 @@ k_step_block(BlockArgs<MODE> args)
     using Plane = BlockPlane<S>;
     constexpr int BX = Plane::BX, BY = Plane::BY;
     constexpr uint32_t ES = sizeof(S);
-    __shared__ Plane P;
-    const StepArgs<MODE>& A = args.A;
-    const BlockGrid& bg = args.bg;
+    const D& A = again<D>(args);
     const Grid& g = A.g;
 
     uint32_t sb, pb, bxi;
-    const uint32_t t = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const uint32_t si = div_rem(t, bg.strip, bg.smagic, sb);
     const bool tail = si >= bg.full;
-    const int z = (int)div_rem(sb, bg.ntx * (tail ? bg.last : bg.ys), tail ? bg.lmagic : bg.pmagic, pb);
-    const int y0 = (int)(si * bg.ys + div_rem(pb, bg.ntx, bg.xmagic, bxi)) * BY;
+    int z = (int)div_rem(sb, bg.ntx * (tail ? bg.last : bg.ys), tail ? bg.lmagic : bg.pmagic, pb);
+    const uint32_t row = div_rem(pb, bg.ntx, bg.xmagic, bxi);
+    const int y0 = (int)(si * bg.ys + row) * BY;
+    // Consecutive workgroups of an XCD go to its shader engines in turn, and
+    // the blocks at an x face take longer than the others: with as many
+    // blocks per row as engines (or half) they would all go to the same
+    // ones.  So each row starts one block further along x (for two blocks
+    // per row every other row): 128^3 with an extrapolating x face, 54.8 us
+    // a step without, 53.0 with (50.0 periodic, where the order stays).
+    if (formed(A.bc.kind[0]) || formed(A.bc.kind[1])) {
+        uint32_t rot;
+        (void)div_rem(bg.ntx == 2 ? row >> 1 : row, bg.ntx, bg.xmagic, rot);
+        bxi += rot;
+        bxi -= bxi >= bg.ntx ? bg.ntx : 0;
+    }
     const int x0 = (int)bxi * BX;
     const int tid = (int)threadIdx.x;
     const int tx = tid % BX, ty = tid / BX;
     const bool act = x0 + tx < g.nx && y0 + ty < g.ny;
     const int kx0 = A.bc.kind[0], kx1 = A.bc.kind[1], ky0 = A.bc.kind[2];
     const int kz0 = A.bc.kind[4], kz1 = A.bc.kind[5];
+    // planes next to a formed z face first: their blocks take longer, and
+    // the launch would end on them
+    if (formed(kz1)) z = z < 2 ? z + g.nz - 2 : z - 2;
 
     // Byte offset of node (xx, yy) from row -2 of its plane: wrapped on
     // periodic axes, in the boundary layers of fixed-state faces (and of
@@ -384,7 +368,7 @@ k_step_block(BlockArgs<MODE> args)
         const int w = v < 0 ? v + g.nz : v >= g.nz ? v - g.nz : v;
         return kz0 != BC_PERIODIC ? v : g.nz == 1 ? 0 : w;
     };
-    auto plane = [&](int zz) { return A.f + (org + (int64_t)zz * g.sz); };
+    auto plane = [&](int zz) { return f + (org + (int64_t)zz * g.sz); };
     const int64_t sv = g.sv;
     auto load = [&](auto ic, const S* base, uint32_t o) {
         constexpr int I = decltype(ic)::value;
@@ -439,7 +423,7 @@ k_step_block(BlockArgs<MODE> args)
     }
     lds_barrier();
 
-    if ((formed(kz0) && z < 2) || (formed(kz1) && z >= g.nz - 2)) block_z_layers<MODE>(z, f0, zm2, zm1, zp1, zp2);
+    if ((formed(kz0) && z < 2) || (formed(kz1) && z >= g.nz - 2)) block_z_layers<MODE, D>(args, z, f0, zm2, zm1, zp1, zp2);
     // (the values converted for the moments there are not kept for those below)
 #pragma unroll
     for (int i = 0; i < NV; i++) asm("" : "+v"(f0[i]));
@@ -450,21 +434,23 @@ k_step_block(BlockArgs<MODE> args)
         axis_diff<I, 2, U2>(f0[I], zm2[I], zm1[I], zp1[I], zp2[I], Dz[I], lz[I]);
     });
 
-    const BlockArgs<MODE>& K = again<MODE>();
+    const D& K = again<D>(args);
     const Model<C>& mc = pick<C>(K.md, K.mf);
     const Model<M>& mm = pick<M>(K.md, K.mf);
     const Macro<M> mac = moments<M, C>(f0, mm);
-    report_health(K.A.health, act ? health_bits(mac) : 0u);
+    report_health(K.health, act ? health_bits(mac) : 0u);
 
-    const bool nearx = kx0 != BC_PERIODIC && (x0 == 0 || K.A.g.nx - x0 <= BX + 1);
-    const bool neary = ky0 != BC_PERIODIC && (y0 == 0 || K.A.g.ny - y0 <= BY + 1);
-    if (nearx || neary) block_layers<MODE>(P, x0, y0, xmem, mac);
+    auto here = [&](int kind) { return formed(kind) || (kind == BC_INFLOW && !xmem); };
+    const bool nearx = (x0 == 0 && here(kx0)) || (K.g.nx - x0 <= BX + 1 && here(kx1));
+    const bool neary = (y0 == 0 && formed(ky0)) || (K.g.ny - y0 <= BY + 1 && formed(K.bc.kind[3]));
+    if (nearx || neary) block_layers<MODE, D>(K, P, Q, x0, y0, xmem, mac);
 
     C feq[NV];
     equilibrium<C, M>(mac, mm, mc, feq);
+    if (nearx || neary) lds_barrier();
     if (!act) return;
-    S* fn = K.A.fn + (K.A.g.org - NG * K.A.g.sy + (int64_t)z * K.A.g.sz);
-    const int64_t svn = K.A.g.sv;
+    S* fn = fout + (K.g.org - NG * K.g.sy + (int64_t)z * K.g.sz);
+    const int64_t svn = K.g.sv;
     uint32_t os = o0;
     asm("" : "+v"(os));
     // places of this thread's neighbours: row -2 of its column (a y step is
@@ -491,6 +477,54 @@ k_step_block(BlockArgs<MODE> args)
         else
             st_lane(sreg(fn + I * svn), os, static_cast<S>(out));
     });
+}
+
+template <int MODE, bool U2, bool PM>
+__global__ void __launch_bounds__(BLOCK_T, MODE == MODE_FP64 ? 2 : 4)
+k_step_block(BlockArgs args)
+{
+    using S = typename Types<MODE>::S;
+    __shared__ BlockPlane<S> P;
+    __shared__ FaceNodes<typename Types<MODE>::M> Q;
+    const uint32_t t = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    step_block<MODE, U2, PM, BlockArgs>(reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr()), args.bg, t,
+                                        (const S*)args.f, (S*)args.fn, P, Q);
+}
+
+// The untiled members of a batch: entry e names the solve of blocks
+// [BATCH_BLOCKS e, BATCH_BLOCKS (e + 1)).
+template <int MODE>
+__global__ void __launch_bounds__(BLOCK_T, MODE == MODE_FP64 ? 2 : 4)
+k_batch_block(const BatchSolve* __restrict__ solves, const BatchTile* __restrict__ entries,
+              const BatchQueue* __restrict__ queue, int parity, const BatchCount* __restrict__ counts)
+{
+    using S = typename Types<MODE>::S;
+    __shared__ BlockPlane<S> P;
+    __shared__ FaceNodes<typename Types<MODE>::M> Q;
+    if (parity < 0 && blockIdx.x == 0) advance_counts(*queue, parity);
+    const uint32_t b = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    // (the tables through the constant address space: scalar loads)
+    const BatchTile& entry = again<BatchTile>(reinterpret_cast<uint64_t>(entries + b / BATCH_BLOCKS));
+    const int m = entry.solve;
+    const uint32_t t = b - (uint32_t)entry.z0;
+    const BlockGrid& bg = again<BlockGrid>(reinterpret_cast<uint64_t>(
+        again<BatchQueue>(reinterpret_cast<uint64_t>(queue)).blocks + m));
+    if (t >= bg.count) return;
+    int par = parity;
+    if (parity < 0) {
+        const BatchCount& c = again<BatchCount>(reinterpret_cast<uint64_t>(counts + m));
+        if (c.done >= c.target) return;
+        par = c.done & 1;
+    }
+    const uint64_t at = reinterpret_cast<uint64_t>(solves + m);
+    const BatchSolve& d = again<BatchSolve>(at);
+    const bool flip = ((d.cur0 ^ par) & 1) != 0;
+    const S* f = (const S*)(flip ? d.f[1] : d.f[0]);
+    S* fn = (S*)(flip ? d.f[0] : d.f[1]);
+    if (d.g.plane_major)
+        step_block<MODE, false, true, BatchSolve>(at, bg, t, f, fn, P, Q);
+    else
+        step_block<MODE, false, false, BatchSolve>(at, bg, t, f, fn, P, Q);
 }
 
 }  // namespace lbm3d

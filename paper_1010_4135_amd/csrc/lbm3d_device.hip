@@ -68,6 +68,7 @@ k_batch_step(const BatchSolve* __restrict__ solves, const BatchTile* __restrict_
     // workgroup b works on list b mod nlists (dispatch places workgroup b on
     // XCD b mod 8, so a list's tiles share one L2); the `per` workgroups of a
     // list take its tiles in order from the list's counter
+    if (parity < 0 && blockIdx.x == 0) advance_counts(*queue, parity);
     const int list = (int)blockIdx.x % nlists;
     const int per = (int)gridDim.x / nlists;
     const int first = queue->first[list];
@@ -119,14 +120,6 @@ k_batch_step(const BatchSolve* __restrict__ solves, const BatchTile* __restrict_
         }
         lds_barrier();  // the plane buffers (and s_k) are reused by the next tile
     }
-}
-
-// Step counts of the batch members after a step: done += 1 while below the
-// target.
-__global__ void __launch_bounds__(64) k_batch_count(BatchCount* __restrict__ counts, int n)
-{
-    const int m = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (m < n && counts[m].done < counts[m].target) counts[m].done += 1;
 }
 
 // Health words of the members of a batch, gathered into one array.
@@ -558,13 +551,6 @@ hipError_t launch_batch_layers(int mode, const BatchSolve* solves, const BatchLa
     return hipGetLastError();
 }
 
-hipError_t launch_batch_count(BatchCount* counts, int n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    k_batch_count<<<dim3(blocks_for(n, 64)), dim3(64), 0, s>>>(counts, n);
-    return hipGetLastError();
-}
-
 template <int MODE, int BY>
 static void launch_batch(unsigned nblocks, bool stream, const BatchSolve* solves, const BatchTile* tiles,
                          BatchQueue* queue, int nlists, int parity, const BatchCount* counts, hipStream_t s)
@@ -581,8 +567,13 @@ hipError_t launch_batch_step(int mode, int by, bool stream, const BatchSolve* so
                              BatchQueue* queue, int nlists, int nblocks, int parity, const BatchCount* counts,
                              hipStream_t s)
 {
-    if (nblocks <= 0 || nlists <= 0 || nlists > BATCH_MAX_LISTS || nblocks % nlists) return hipErrorInvalidValue;
     if (parity < 0 && !counts) return hipErrorInvalidValue;
+    if (by == 0) {
+        if (nblocks <= 0 || nblocks % BATCH_BLOCKS) return hipErrorInvalidValue;
+        launch_batch_blocks(mode, nblocks, solves, tiles, queue, parity, counts, s);
+        return hipGetLastError();
+    }
+    if (nblocks <= 0 || nlists <= 0 || nlists > BATCH_MAX_LISTS || nblocks % nlists) return hipErrorInvalidValue;
     // the batch's tile heights: 4 rows in FP64, 8 in the FP32 modes
     if (by != (mode == MODE_FP64 ? 4 : 8)) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)nblocks;

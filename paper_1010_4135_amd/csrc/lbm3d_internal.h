@@ -78,6 +78,26 @@ struct BatchTile {
     int32_t z0, z1;       // z range
 };
 
+// Blocks of the untiled kernel in one level, numbered strip by strip: a strip
+// is `ys` block rows of every plane (the last one what is left), its blocks
+// numbered x fastest, then y, then z.  (The magics divide: see div_magic.)
+constexpr int BLOCK_T = 256, BLOCK_X = 32, BLOCK_Y = BLOCK_T / BLOCK_X;  // threads; nodes along x and y
+struct BlockGrid {
+    uint32_t ntx, ys, strip, full, last;  // blocks: per row, rows of a strip, per strip, strips of ys rows, rows left
+    uint32_t count;                       // in all
+    uint32_t xmagic, smagic, pmagic, lmagic;
+};
+BlockGrid block_grid(const Grid& g);
+
+// Step count of a batch member within a run of the batched step: it takes
+// part in the launches while done < target, and its current buffer is
+// cur0 ^ (done & 1).  The counts are held twice: a step reads one copy and
+// its kernels write the other, advanced, for the next step.
+struct BatchCount {
+    int32_t done;
+    int32_t target;
+};
+
 // Work lists of the batched step: the tiles are split into `nlists` lists
 // (one per XCD), list l holding tiles [first[l], first[l + 1]); the
 // workgroups of a list take its tiles in order from a counter.
@@ -85,7 +105,14 @@ constexpr int BATCH_MAX_LISTS = 8;
 struct BatchQueue {
     int32_t first[BATCH_MAX_LISTS + 1];
     uint32_t next[BATCH_MAX_LISTS];  // zero between launches
+    const BlockGrid* blocks;         // per member, for those the untiled kernel steps
+    BatchCount* counts;              // both copies, members each
+    int32_t members;
 };
+// Blocks per entry of the untiled kernel's part of a batch (every member's
+// block count is rounded up to whole entries): the entry names the member
+// (solve) and its first block (z0).
+constexpr int BATCH_BLOCKS = 64;
 
 // Per-solve entry of the batched step (device memory, read uniformly).
 struct BatchSolve {
@@ -101,14 +128,6 @@ struct BatchSolve {
 
 // One solve's share of the batched boundary-layer launch: workgroups
 // [first, next job's first) of 64 lines each over the faces in `faces`.
-// Step count of a batch member within a run of the batched step: it takes
-// part in the launches while done < target, and its current buffer is
-// cur0 ^ (done & 1).  A counting launch after each step advances done.
-struct BatchCount {
-    int32_t done;
-    int32_t target;
-};
-
 struct BatchLayerJob {
     int32_t solve;
     uint32_t faces;
@@ -152,7 +171,10 @@ hipError_t launch_step(int mode, const Grid& g, const FaceBC& bc, const TileCfg&
                        const Model<float>& mf, const double (*inflow)[5], const void* f, void* fn,
                        uint32_t* health, hipStream_t s, bool upwind2 = false, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
-// The untiled kernel's launch (launch_step with tc.by == 0).
+// The untiled kernel's launches (launch_step with tc.by == 0,
+// launch_batch_step with by == 0).
+void launch_batch_blocks(int mode, int nblocks, const BatchSolve* solves, const BatchTile* entries,
+                         const BatchQueue* queue, int parity, const BatchCount* counts, hipStream_t s);
 void launch_block(int mode, const Grid& g, const FaceBC& bc, const Model<double>& md, const Model<float>& mf,
                   const double (*inflow)[5], const void* f, void* fn, uint32_t* health, hipStream_t s, bool upwind2,
                   hipEvent_t ev_start, hipEvent_t ev_stop);
@@ -173,17 +195,18 @@ hipError_t launch_pack(int mode, const Grid& g, const void* f, void* dense, bool
 // list (device); `parity` selects f[cur0 ^ parity] as the current level.
 // Boundary layers of the members of a batch after a step (one launch).
 // parity >= 0: every member steps from its buffer of that parity (relative
-// to build); parity < 0: each member steps per its BatchCount (see above).
+// to build); parity < 0: each member steps per its BatchCount in `counts`,
+// the first copy (-1) or the second (-2).
 hipError_t launch_batch_layers(int mode, const BatchSolve* solves, const BatchLayerJob* jobs, const int32_t* block_job,
                                int nblocks, int parity, const BatchCount* counts, hipStream_t s);
-// done += 1 for each of the n members with done < target.
-hipError_t launch_batch_count(BatchCount* counts, int n, hipStream_t s);
 // out[k] = the health word of member k (n members).
 hipError_t launch_gather_health(const BatchSolve* solves, int n, uint32_t* out, hipStream_t s);
-// One step of every member (parity as for launch_batch_layers): `nblocks`
-// persistent workgroups (a multiple of `nlists`); workgroup b works on list
-// b mod nlists.  `stream`: the store kind of the new level (see
-// STREAM_MIN_BYTES).
+// One step of every tiled member (parity as for launch_batch_layers):
+// `nblocks` persistent workgroups (a multiple of `nlists`); workgroup b works
+// on list b mod nlists.  `stream`: the store kind of the new level (see
+// STREAM_MIN_BYTES).  With by == 0, of the untiled members: `nblocks` blocks,
+// `tiles` their entries (one per BATCH_BLOCKS blocks).  Either writes the
+// counts of the next step.
 hipError_t launch_batch_step(int mode, int by, bool stream, const BatchSolve* solves, const BatchTile* tiles,
                              BatchQueue* queue, int nlists, int nblocks, int parity, const BatchCount* counts,
                              hipStream_t s);

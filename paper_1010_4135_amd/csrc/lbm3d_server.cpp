@@ -283,7 +283,7 @@ void lbm3d_server::run()
                     k = std::max(k, std::min(tick_steps, t->left));
                 }
             if (members.empty() || k <= 0) continue;
-            const bool fresh = rebuild || plans[mode].ntiles() == 0;
+            const bool fresh = rebuild || plans[mode].empty();
             if (fresh) {
                 const auto tp = Clock::now();
                 // (tile depth from the launch model for this membership)

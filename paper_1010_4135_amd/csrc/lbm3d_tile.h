@@ -665,6 +665,19 @@ __device__ __forceinline__ void step_tile(const StepArgs<MODE>& A, const Model<d
         step_tile_x<MODE, BY, false, VK, NT>(A, md, mf, x0, y0, z0, z1, P);
 }
 
+// The members' counts for the next step of a batch, from this step's (one
+// workgroup; nothing in this step reads the copy written).
+__device__ __forceinline__ void advance_counts(const BatchQueue& q, int parity)
+{
+    const BatchCount* in = q.counts + (parity == -1 ? 0 : q.members);
+    BatchCount* out = q.counts + (parity == -1 ? q.members : 0);
+    for (int m = (int)threadIdx.x; m < q.members; m += (int)blockDim.x) {
+        BatchCount c = in[m];
+        if (c.done < c.target) c.done += 1;
+        out[m] = c;
+    }
+}
+
 // Tile order: tiles are numbered with x (or y) fastest, then the other
 // axis, then the z chunk, and consecutive numbers are given to workgroups
 // that land on the same XCD (dispatch assigns workgroup b to XCD b mod 8),
