@@ -116,12 +116,8 @@ __device__ __forceinline__ Macro<M> pick_macro(bool first, const Macro<M>& a, co
     return q;
 }
 
-// What the step of a solve is described by: the kernel's argument segment
-// (BlockArgs), or the solve's entry in a batch's table (BatchSolve).  Held in
-// scalar registers from the first use to the last, this would overflow the
-// scalar file (the model constants alone are 40 dwords in double) and be
-// spilled into vector lanes; `again` makes later uses read it once more,
-// through the scalar cache, instead.
+// What the step of a solve is described by, in the kernel's argument segment
+// (a member of a batch: its entry of the solve table).
 struct BlockArgs {
     Grid g;
     FaceBC bc;
@@ -133,14 +129,6 @@ struct BlockArgs {
     void* fn;
     uint32_t* health;
 };
-template <typename D>
-__device__ __forceinline__ const D& again(uint64_t at)
-{
-    using AP = const __attribute__((address_space(4))) D*;
-    asm volatile("" : "+s"(at));
-    return *(const D*)reinterpret_cast<AP>(at);
-}
-
 __device__ __forceinline__ constexpr bool formed(int kind) { return kind == BC_OUTFLOW || kind == BC_REFLECT; }
 
 // Moments of a block's nodes next to its x and y faces, by face side, the

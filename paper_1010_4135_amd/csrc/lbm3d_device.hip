@@ -22,8 +22,10 @@ namespace lbm3d {
 
 template <int MODE, int BY, bool NT>
 __global__ void __launch_bounds__(TILE_X * BY)
-k_step_tiled(StepArgs<MODE> A, Model<double> md, Model<float> mf, int ntx, int nty, int tz)
+k_step_tiled(TileArgs<MODE> args)
 {
+    const StepArgs<MODE>& A = args.A;
+    const int ntx = args.ntx, nty = args.nty, tz = args.tz;
     __shared__ TilePlane<BY, typename Types<MODE>::S> P[2];
     const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     // tiles numbered x fastest, then y, then the z chunk
@@ -33,7 +35,8 @@ k_step_tiled(StepArgs<MODE> A, Model<double> md, Model<float> mf, int ntx, int n
     const int tzi = r / nty;
     const int z0 = tzi * tz;
     const int z1 = min(z0 + tz, A.g.nz);
-    step_tile<MODE, BY, true, NT>(A, md, mf, txi * TILE_X, tyi * BY, z0, z1, P);
+    step_tile<MODE, BY, NT, TileArgs<MODE>>(A, reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr()),
+                                            txi * TILE_X, tyi * BY, z0, z1, P);
 }
 
 // Batched fused step: persistent workgroups walk a packed list of tiles from
@@ -48,15 +51,6 @@ __device__ __forceinline__ void keep(T& v)
 {
     asm volatile("" : "+s"(v));
 }
-template <typename T>
-__device__ __forceinline__ void keep_model(Model<T>& m)
-{
-    keep(m.c1); keep(m.k); keep(m.c1sq); keep(m.c2sq); keep(m.e0sq); keep(m.inv_b); keep(m.r_aT);
-    keep(m.x_a0); keep(m.x_aT); keep(m.x_au); keep(m.x_b0); keep(m.x_bT); keep(m.x_bu); keep(m.x_d);
-    keep(m.d_a0); keep(m.d_aT); keep(m.d_au); keep(m.d_b0); keep(m.d_bT); keep(m.d_bu); keep(m.d_d);
-    keep(m.k_adv); keep(m.k_bgk); keep(m.k_lap0); keep(m.k_lap1); keep(m.a1); keep(m.ad);
-}
-
 template <int MODE, int BY, bool NT>
 __global__ void __launch_bounds__(TILE_X * BY)
 k_batch_step(const BatchSolve* __restrict__ solves, const BatchTile* __restrict__ tiles, BatchQueue* queue,
@@ -83,10 +77,12 @@ k_batch_step(const BatchSolve* __restrict__ solves, const BatchTile* __restrict_
             s_k = k;
         }
         __syncthreads();
-        const int k = s_k;
+        const int k = __builtin_amdgcn_readfirstlane(s_k);
         if (k >= cnt) break;
-        const BatchTile tile = tiles[first + k];
-        const BatchSolve& d = solves[tile.solve];
+        // (the tables through the constant address space: scalar loads)
+        const BatchTile& tile = again<BatchTile>(reinterpret_cast<uint64_t>(tiles + first + k));
+        const uint64_t at = reinterpret_cast<uint64_t>(solves + tile.solve);
+        const BatchSolve& d = again<BatchSolve>(at);
         // the member's parity: given (timing trials), or from its own step
         // count, which also says whether it still steps in this run (the
         // same for the whole workgroup, so the barriers stay uniform)
@@ -107,16 +103,11 @@ k_batch_step(const BatchSolve* __restrict__ solves, const BatchTile* __restrict_
             A.health = d.health;
 #pragma unroll
             for (int j = 0; j < 10; j++) A.xin[j / 5][j % 5] = d.xin[j / 5][j % 5];
-            Model<double> md = d.md;
-            Model<float> mf = d.mf;
-            // the tile's solve is read once per tile: without this the
-            // compiler re-loads its constants and strides from the table in
-            // every plane, each a scalar-memory round trip the plane then
-            // waits for
+            // the tile's strides and pointers are read once per tile: without
+            // this the compiler re-loads them from the table in every plane
             keep(A.g.sy); keep(A.g.sz); keep(A.g.sv); keep(A.g.org); keep(A.g.sink); keep(A.g.xg);
             keep(A.f); keep(A.fn);
-            keep_model(mf);
-            step_tile<MODE, BY, true, NT>(A, md, mf, tile.txi * TILE_X, tile.tyi * BY, tile.z0, tile.z1, P);
+            step_tile<MODE, BY, NT, BatchSolve>(A, at, tile.txi * TILE_X, tile.tyi * BY, tile.z0, tile.z1, P);
         }
         lds_barrier();  // the plane buffers (and s_k) are reused by the next tile
     }
@@ -416,24 +407,28 @@ static void launch_tiled(const Grid& g, const FaceBC& bc, int tz, bool stream, c
     const int nty = (g.ny + BY - 1) / BY;
     const int ntz = (g.nz + tz - 1) / tz;
     const int nb = ntx * nty * ntz;
-    StepArgs<MODE> A;
-    A.g = g;
-    A.bc = bc;
-    A.f = (const S*)f;
-    A.fn = (S*)fn;
-    A.health = health;
-    x_fixed_states(inflow, A.xin);
+    TileArgs<MODE> K;
+    K.A.g = g;
+    K.A.bc = bc;
+    K.A.f = (const S*)f;
+    K.A.fn = (S*)fn;
+    K.A.health = health;
+    x_fixed_states(inflow, K.A.xin);
+    K.md = md;
+    K.mf = mf;
+    K.ntx = ntx;
+    K.nty = nty;
+    K.tz = tz;
     const dim3 grid(nb), block(TILE_X * BY);
     if (e0 || e1) {
         if (stream)
-            hipExtLaunchKernelGGL(k_step_tiled<MODE, BY, true>, grid, block, 0, s, e0, e1, 0, A, md, mf, ntx, nty, tz);
+            hipExtLaunchKernelGGL(k_step_tiled<MODE, BY, true>, grid, block, 0, s, e0, e1, 0, K);
         else
-            hipExtLaunchKernelGGL(k_step_tiled<MODE, BY, false>, grid, block, 0, s, e0, e1, 0, A, md, mf, ntx, nty,
-                                  tz);
+            hipExtLaunchKernelGGL(k_step_tiled<MODE, BY, false>, grid, block, 0, s, e0, e1, 0, K);
     } else if (stream) {
-        k_step_tiled<MODE, BY, true><<<grid, block, 0, s>>>(A, md, mf, ntx, nty, tz);
+        k_step_tiled<MODE, BY, true><<<grid, block, 0, s>>>(K);
     } else {
-        k_step_tiled<MODE, BY, false><<<grid, block, 0, s>>>(A, md, mf, ntx, nty, tz);
+        k_step_tiled<MODE, BY, false><<<grid, block, 0, s>>>(K);
     }
 }
 

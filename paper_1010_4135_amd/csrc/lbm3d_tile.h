@@ -85,7 +85,7 @@ __host__ __device__ constexpr HaloJobs make_halo_jobs()
 }
 __constant__ const HaloJobs kHaloJobs = make_halo_jobs();
 
-// Everything a tile needs about its solve.
+// Everything a tile needs about its solve but the model constants.
 template <int MODE>
 struct StepArgs {
     using S = typename Types<MODE>::S;
@@ -147,6 +147,15 @@ __device__ __forceinline__ __attribute__((address_space(1))) S* gptr(S* p)
 {
     return reinterpret_cast<__attribute__((address_space(1))) S*>(reinterpret_cast<uint64_t>(p));
 }
+
+// The tiled kernel's arguments.
+template <int MODE>
+struct TileArgs {
+    StepArgs<MODE> A;
+    Model<double> md;
+    Model<float> mf;
+    int32_t ntx, nty, tz;
+};
 
 template <typename P, typename C>
 __device__ __forceinline__ void store_node(P fn, int64_t sv, uint32_t off, const C (&v)[NV])
@@ -302,34 +311,53 @@ __device__ __forceinline__ Macro<M> shfl_macro(const Macro<M>& q, int l)
     return r;
 }
 
+// The description of a solve's step at address `at` (the kernel's argument
+// segment, or the solve's entry in a batch's table), to be read through the
+// scalar cache from here on.  Held in scalar registers from the first use to
+// the last, it would overflow the scalar file (the model constants alone are
+// 40 dwords in double) and be spilled into vector lanes; each `again` makes
+// the uses after it read it once more instead.
+template <typename D>
+__device__ __forceinline__ const D& again(uint64_t at)
+{
+    using AP = const __attribute__((address_space(4))) D*;
+    asm volatile("" : "+s"(at));
+    return *(const D*)reinterpret_cast<AP>(at);
+}
+
 // XF: this tile forms extrapolating or reflecting x layers itself (see
-// x_forms(); the caller selects the instantiation per tile).  VK: the FP64
-// model constants may be held in vector registers (see below).  NT: the new
-// level is stored non-temporally (see st_at).
-template <int MODE, int BY, bool XF, bool VK, bool NT>
-__device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, const Model<double>& md,
-                                            const Model<float>& mf, int x0, int y0, int z0, int z1,
+// x_forms(); the caller selects the instantiation per tile).  NT: the new
+// level is stored non-temporally (see st_at).  D at `at` holds the model
+// constants (md, mf).
+template <int MODE, int BY, bool XF, bool NT, typename D>
+__device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, uint64_t at, int x0, int y0, int z0, int z1,
                                             TilePlane<BY, typename Types<MODE>::S> (&P)[2])
 {
     using S = typename Types<MODE>::S;
     using C = typename Types<MODE>::C;
     using M = typename Types<MODE>::M;
     constexpr uint32_t ES = sizeof(S);
-    const Model<C>& mc = pick<C>(md, mf);
-    Model<M> mm = pick<M>(md, mf);
-    if constexpr (VK && MODE == MODE_FP32_T64 && BY >= 8) {
-        // Uniform FP64 constants held in vector registers.  The scalar
-        // file cannot hold them beside the pointers and loop state, and the
-        // compiler would spill them into vector lanes and read them back
-        // (one VALU instruction per dword) in every plane.  The 8-row
-        // tiles have the vector registers to spare at two wavefronts per
-        // SIMD; the smaller tiles do not, and FP32 constants fit the
-        // scalar file.
+    // The model constants.  In FP32 they are read once more in every plane:
+    // held throughout, they spill the scalar file, and each plane reads some
+    // 100 of its dwords back from vector lanes (256x128x128: 111.1 us a step
+    // held, 108.8 read again; 128^3 53.8 and 52.0).  A double constant takes
+    // two scalar registers, and an instruction one scalar operand only, so
+    // the double models gain nothing from the scalar file: the 8-row tiles
+    // hold theirs in vector registers, which they have to spare at two
+    // wavefronts per SIMD (256x128x128: 122.6 us read again, 114.5 held); the
+    // 4-row FP64 tiles hold theirs wherever the compiler puts them (read
+    // again: 128^3 level, 256x128x128 260 us against 253).
+    constexpr bool REREAD = MODE == MODE_FP32;
+    const D& once = again<D>(at);
+    const Model<C> c_once = pick<C>(once.md, once.mf);
+    Model<M> m_once = pick<M>(once.md, once.mf);
+    if constexpr (MODE == MODE_FP32_T64 && BY >= 8) {
         auto vk = [](M& v) { asm volatile("" : "+v"(v)); };
-        vk(mm.r_aT);
-        vk(mm.x_a0); vk(mm.x_aT); vk(mm.x_au); vk(mm.x_b0); vk(mm.x_bT); vk(mm.x_bu);
-        vk(mm.d_a0); vk(mm.d_aT); vk(mm.d_au); vk(mm.d_b0); vk(mm.d_bT); vk(mm.d_bu);
-        vk(mm.c1); vk(mm.k); vk(mm.e0sq); vk(mm.c1sq); vk(mm.c2sq); vk(mm.inv_b); vk(mm.x_d); vk(mm.d_d);
+        vk(m_once.r_aT);
+        vk(m_once.x_a0); vk(m_once.x_aT); vk(m_once.x_au); vk(m_once.x_b0); vk(m_once.x_bT); vk(m_once.x_bu);
+        vk(m_once.d_a0); vk(m_once.d_aT); vk(m_once.d_au); vk(m_once.d_b0); vk(m_once.d_bT); vk(m_once.d_bu);
+        vk(m_once.c1); vk(m_once.k); vk(m_once.e0sq); vk(m_once.c1sq); vk(m_once.c2sq); vk(m_once.inv_b);
+        vk(m_once.x_d); vk(m_once.d_d);
     }
     const Grid& g = A.g;
     const S* __restrict__ f = A.f;
@@ -484,7 +512,7 @@ __device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, const Model
             qf.uz = static_cast<M>(side ? A.xin[1][3] : A.xin[0][3]);
             qf.T = static_cast<M>(side ? A.xin[1][4] : A.xin[0][4]);
             C e[NV];
-            equilibrium<C, M>(qf, mm, mc, e);
+            equilibrium<C, M>(qf, m_once, c_once, e);
             if (tx < 4 && (side ? rfix : lfix)) {
                 const int colw = tx == 0 ? 1 : tx == 1 ? 0 : tx + TILE_X;
 #pragma unroll
@@ -502,7 +530,7 @@ __device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, const Model
     // that layer node (a halo column, or past a ragged +x face a column of
     // the row itself, overwriting what the lane there staged), which only
     // this wavefront reads (so no barrier orders it)
-    auto form_x = [&](const Macro<M>& mq, TilePlane<BY, S>& T) {
+    auto form_x = [&](const Macro<M>& mq, const Model<M>& mm, TilePlane<BY, S>& T) {
         const int side = tx >> 5, ll = tx & 31;
         const int j = ll >= NV ? 1 : 0, iv = min(ll - NV * j, NV - 1);
         const int kind = side ? kR : kL;
@@ -550,6 +578,9 @@ __device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, const Model
         load_halo(K & 1, za);
         za = znext(za);
         zb = znext(zb);
+        const D& args = REREAD ? again<D>(at) : once;
+        const Model<C>& mc = REREAD ? pick<C>(args.md, args.mf) : c_once;
+        const Model<M>& mm = REREAD ? pick<M>(args.md, args.mf) : m_once;
         lds_barrier();
 
         C fc[NV];
@@ -562,7 +593,7 @@ __device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, const Model
         // on tiles that form x layers (their own copy of the sweep, so no
         // branch keeps the scheduler from interleaving it with the node's
         // equilibrium) the layers of this plane come first
-        if constexpr (XF) form_x(mac, cur);
+        if constexpr (XF) form_x(mac, mm, cur);
         C feq[NV];
         equilibrium<C, M>(mac, mm, mc, feq);
         const uint32_t outb = act ? colb : (uint32_t)((sinkrel - (int64_t)z * sz) * ES) + (uint32_t)tx * ES;
@@ -654,15 +685,14 @@ __device__ __forceinline__ bool x_forms(const StepArgs<MODE>& A, int x0)
     return (x0 == 0 && formed(A.bc.kind[0])) || (xr <= TILE_X && xr >= 2 && formed(A.bc.kind[1]));
 }
 
-template <int MODE, int BY, bool VK, bool NT>
-__device__ __forceinline__ void step_tile(const StepArgs<MODE>& A, const Model<double>& md,
-                                          const Model<float>& mf, int x0, int y0, int z0, int z1,
+template <int MODE, int BY, bool NT, typename D>
+__device__ __forceinline__ void step_tile(const StepArgs<MODE>& A, uint64_t at, int x0, int y0, int z0, int z1,
                                           TilePlane<BY, typename Types<MODE>::S> (&P)[2])
 {
     if (x_forms(A, x0))
-        step_tile_x<MODE, BY, true, VK, NT>(A, md, mf, x0, y0, z0, z1, P);
+        step_tile_x<MODE, BY, true, NT, D>(A, at, x0, y0, z0, z1, P);
     else
-        step_tile_x<MODE, BY, false, VK, NT>(A, md, mf, x0, y0, z0, z1, P);
+        step_tile_x<MODE, BY, false, NT, D>(A, at, x0, y0, z0, z1, P);
 }
 
 // The members' counts for the next step of a batch, from this step's (one
