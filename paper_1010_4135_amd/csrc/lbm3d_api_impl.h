@@ -32,6 +32,7 @@ struct lbm3d_solver {
     hipStream_t stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+    lbm3d_solver();
     ~lbm3d_solver();
 };
 
@@ -48,6 +49,24 @@ size_t f_bytes(const Grid& g, int precision);
 size_t footprint_of(const lbm3d_params* p);
 int32_t solver_create(const lbm3d_params* p, lbm3d_solver** out);
 int32_t solver_enqueue_steps(lbm3d_solver* h, int64_t nsteps);
+// ---- host copies (lbm3d_api.cpp) ----
+// dst[0 .. n) = src[0 .. n), by several threads where that pays.
+void copy_host(double* dst, const double* src, size_t n);
+struct HostCopy {
+    void* host;
+    void* dev;
+    size_t bytes;
+};
+// Copies between caller memory and the device, after the work on s.  To the
+// host: complete when s has been waited for; from it: the host memory may be
+// reused when the call returns.
+hipError_t copy_to_host(const HostCopy* items, int n, hipStream_t s);
+hipError_t copy_to_device(const HostCopy* items, int n, hipStream_t s);
+// The pinned buffer those copies go through exists while a user of it does
+// (every solver and server is one).
+void staging_ref();
+void staging_unref();
+
 // Stability admission of an initial state (lbm3d_admit): E_UNSTABLE if the
 // von Neumann analysis at the state's extremes exceeds 1 + STABILITY_TOL.
 constexpr double STABILITY_TOL = 1e-3;

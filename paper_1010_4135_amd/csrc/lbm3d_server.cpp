@@ -28,8 +28,9 @@ constexpr int64_t GRAPH_AFTER_TICKS = 8;
 struct Ticket {
     uint64_t id = 0;
     lbm3d_params p{};
-    std::vector<double> in[5];
-    std::vector<double> out[5];
+    size_t n = 0;                        // nodes
+    std::unique_ptr<double[]> in[5];     // initial fields until admitted
+    std::unique_ptr<double[]> out[5];    // results
     int64_t nsteps = 0, left = 0;
     size_t footprint = 0;
     lbm3d_solver* h = nullptr;
@@ -85,6 +86,8 @@ struct lbm3d_server {
     int64_t plan_ticks[3] = {0, 0, 0};  // ticks each plan has run since it was built
     lbm3d_server_counters stats{};  // guarded by mu
 
+    lbm3d_server() { lbm3d::staging_ref(); }
+    ~lbm3d_server() { lbm3d::staging_unref(); }
     double now() const { return std::chrono::duration<double>(Clock::now() - t0).count(); }
     void run();
     void help();
@@ -109,10 +112,18 @@ void lbm3d_server::finish(Ticket* t, int32_t status)
     const auto tf = Clock::now();
     if (t->h) {
         if (status == LBM3D_OK || status == LBM3D_E_NONFINITE) {
-            const int64_t n = t->h->n;
-            for (int c = 0; c < 5; c++) t->out[c].resize((size_t)n);
-            int32_t rc = lbm3d_moments(t->h, t->out[0].data(), t->out[1].data(), t->out[2].data(),
-                                       t->out[3].data(), t->out[4].data());
+            // (not zeroed: the read-back fills them)
+            bool ok = true;
+            for (auto& v : t->out) {
+                v.reset(new (std::nothrow) double[t->n]);
+                ok = ok && v;
+            }
+            int32_t rc = ok ? lbm3d_moments(t->h, t->out[0].get(), t->out[1].get(), t->out[2].get(), t->out[3].get(),
+                                            t->out[4].get())
+                            : LBM3D_E_NOMEM;
+            if (rc != LBM3D_OK && rc != LBM3D_E_NONFINITE)
+                for (auto& v : t->out)
+                    if (v) std::memset(v.get(), 0, t->n * sizeof(double));
             if (status == LBM3D_OK) status = rc;
         }
         uint32_t hw = 0;
@@ -141,8 +152,8 @@ void lbm3d_server::admit_one(Ticket* t)
     int32_t rc = lbm3d_create(&t->p, &h);
     if (rc == LBM3D_OK) rc = lbm3d_set_stream(h, side);
     if (rc == LBM3D_OK)
-        rc = lbm3d_init(h, t->in[0].data(), t->in[1].data(), t->in[2].data(), t->in[3].data(), t->in[4].data());
-    for (auto& v : t->in) std::vector<double>().swap(v);
+        rc = lbm3d_init(h, t->in[0].get(), t->in[1].get(), t->in[2].get(), t->in[3].get(), t->in[4].get());
+    for (auto& v : t->in) v.reset();
     t->h = h;
     if (rc != LBM3D_OK) {
         finish(t, rc);
@@ -402,7 +413,11 @@ int32_t lbm3d_server_submit(lbm3d_server_t s, const lbm3d_params* p, const doubl
     t->p = *p;
     const double* src[5] = {rho, ux, uy, uz, pr};
     try {
-        for (int c = 0; c < 5; c++) t->in[c].assign(src[c], src[c] + n);
+        t->n = n;
+        for (int c = 0; c < 5; c++) {
+            t->in[c].reset(new double[n]);
+            lbm3d::copy_host(t->in[c].get(), src[c], n);
+        }
     } catch (...) {
         return LBM3D_E_NOMEM;
     }
@@ -450,7 +465,7 @@ int32_t lbm3d_server_wait(lbm3d_server_t s, uint64_t ticket, double* rho, double
     }
     double* dst[5] = {rho, ux, uy, uz, p};
     for (int c = 0; c < 5; c++)
-        if (dst[c] && !t->out[c].empty()) std::memcpy(dst[c], t->out[c].data(), t->out[c].size() * sizeof(double));
+        if (dst[c] && t->out[c]) lbm3d::copy_host(dst[c], t->out[c].get(), t->n);
     if (tm) {
         tm->t_submit = t->t_submit;
         tm->t_admit = t->t_admit;
