@@ -406,14 +406,17 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         std::vector<BatchTile> items;
         if (part.tiled) {
             std::vector<Grid> grids;
-            int64_t level_bytes = 0;
+            int64_t level_bytes = 0, dense_bytes = 0;
             for (lbm3d_solver* h : mine) {
                 grids.push_back(h->g);
-                level_bytes += 2 * (int64_t)f_bytes(h->g, h->mode);
+                const int64_t bytes = 2 * (int64_t)f_bytes(h->g, h->mode);
+                level_bytes += bytes;
+                if (dense_rows(h->g.nx) || mode_ == LBM3D_FP64) dense_bytes += bytes;
             }
             // plain stores when the levels together fit the memory-side
-            // cache, as for a single solve
-            q.stream = level_bytes > STREAM_MIN_BYTES;
+            // cache, or most of them have rows that end inside a cache
+            // line (in the FP32 modes), as for a single solve
+            q.stream = level_bytes > STREAM_MIN_BYTES && 2 * dense_bytes > level_bytes;
             TilePlan plan;
             int32_t rc = plan_tiles(grids, by_, plan_depth(mode_, tz, grids, by_, cus), cus, plan);
             if (rc) {

@@ -149,8 +149,14 @@ struct TileCfg {
 // levels that fits the 256 MB memory-side cache is read back from it by the
 // next step when stored plainly (the step on the 298x78x78 grid, 240 MB,
 // takes 61 us against 85 us streaming); larger ones gain nothing there and
-// streaming keeps the L2 for the halo planes.  The autotuner tries both.
+// streaming keeps the L2 for the halo planes.  Only with dense rows: where a
+// row ends inside a cache line, its streamed part goes out as partial writes
+// (150^3 FP32 182 us streaming, 134 plain; 200x200x100 203 and 150; FP64
+// 150^3 322 and 278, 300x150x100 311 and 284).  FP64 levels of up to twice
+// the limit are the exception (180x90x95, 370 MB, 134 us streaming and 141
+// plain; 298x78x78, 435 MB, 121 and 125).  The autotuner tries both.
 constexpr int64_t STREAM_MIN_BYTES = (int64_t)320 << 20;
+bool stream_rows(const Grid& g, int mode);
 TileCfg default_tile(int mode, const Grid& g);
 // compute units of the current device (256 when it cannot be asked)
 int device_cus();

@@ -148,45 +148,70 @@ int device_cus()
     return cache[(size_t)dev];
 }
 
+bool stream_rows(const Grid& g, int mode)
+{
+    const int64_t bytes = 2 * (int64_t)f_bytes(g, mode);
+    return bytes > STREAM_MIN_BYTES && (dense_rows(g.nx) || (mode == MODE_FP64 && bytes <= 2 * STREAM_MIN_BYTES));
+}
+
+// The launch shape of a solve that is not tuned, from a model of the two
+// kernels (256 compute units, us a step; the autotuner remains the way to the
+// best shape).
+//
+// Tiled, 64 x BY columns (BY = 8 in the FP32 modes, 4 in FP64, the rows that
+// fit two wavefronts per SIMD) of `d` planes, every chunk count whose d is 8
+// or more: the tiles run in rounds of one per compute unit, and a tile takes
+// time in proportion to its planes plus the four its z ring loads first; one
+// of its planes takes 2.4 us in the FP32 modes while both levels stay in the
+// 256 MB memory-side cache (2.33 - 2.46 over 10 grids) and 2.8 beyond (2.67 -
+// 2.92 over 6), 2.95 in FP64 (2.78 - 3.1 over 14).  The cheapest d wins, in
+// FP64 as it is; in the FP32 modes, whose tiles lean more on the caches, the
+// deepest within an eighth of it: a round more means more halo planes read
+// again (FP32 200x200x100: two rounds of 20 planes 159 us, one of 50 150;
+// 300x150x100 167 and 152).  Against depths of powers of two only: FP32
+// 160^3 157 -> 123 us, 192x128x128 93.9 -> 83.7; FP64 250x120x33 101 -> 60.
+//
+// Untiled, per 1000 nodes of its 32 x 8 blocks: 25 ns (24 - 27) in the FP32
+// modes and 60 in FP64 in that cache, 39 and 77 beyond.  Its small blocks
+// spread over all units whatever the grid, so it wins where the tiles fill
+// their rounds badly: FP32 150x100x70 31 us (tiles of 12 planes 38),
+// 384x96x50 44.6 (49.2), FP64 100x61x50 29 (34).  Where the tiles fill 95%
+// of their rounds the two models are mostly within their own error (FP32
+// 128^3 52 and 52, 512x64x48 38.6 tiled and 39.3, 128x128x64 29.5 and 27.0)
+// and the tiles stay; 96x64x64 FP64, 37 us tiled and 28 untiled, is the
+// grid that pays for this line.
+constexpr int64_t CACHED_BYTES = (int64_t)256 << 20;
+
 TileCfg default_tile(int mode, const Grid& g)
 {
-    // Tiles of 64 x BY columns (BY = 8 in the FP32 modes, 4 in FP64, the
-    // rows that fit two wavefronts per SIMD) and a z-chunk depth from a
-    // simple launch model: the tiles run in rounds of one per compute unit,
-    // and a tile takes time in proportion to its planes plus the four
-    // planes its z ring loads first; the depth with the lowest cost wins
-    // (the longer one on a tie).  When even the shortest useful chunks (8
-    // planes) leave more than a quarter of the compute units without a
-    // tile, the untiled kernel, whose small blocks spread over all of
-    // them, is faster.  These choices match the autotuner's on the grids it
-    // was compared on (256x128x128, 192x128x128, 128^3 and the paper's
-    // 298x78x78 tile; grids up to 96x64x64 in the FP32 modes and up to 64^3
-    // in FP64 untiled), which remains the way to the best shape.
     TileCfg t;
     t.by = 0;
     t.tz = 1;
     if (!tiled_fits(mode, g)) return t;
-    const int64_t es = mode == MODE_FP64 ? 8 : 4;
-    t.stream = 2 * g.len * es > STREAM_MIN_BYTES;
-    const int by = mode == MODE_FP64 ? 4 : 8;
+    t.stream = stream_rows(g, mode);
+    const bool fp64 = mode == MODE_FP64;
+    const bool cached = 2 * (int64_t)f_bytes(g, mode) <= CACHED_BYTES;
+    const int by = fp64 ? 4 : 8;
     const int64_t cus = device_cus();
     const int64_t cols = (int64_t)((g.nx + TILE_X - 1) / TILE_X) * ((g.ny + by - 1) / by);
-    int best_tz = 0;
-    int64_t best_cost = 0, best_tiles = 0;
-    for (int64_t tz = 8;; tz *= 2) {
-        const int64_t d = std::min<int64_t>(tz, g.nz);
-        const int64_t tiles = cols * ((g.nz + d - 1) / d);
-        const int64_t cost = ((tiles + cus - 1) / cus) * (d + 4);
-        if (best_tz == 0 || cost <= best_cost) {
-            best_tz = (int)d;
-            best_cost = cost;
-            best_tiles = tiles;
-        }
-        if (d >= g.nz) break;
+    const auto tiles_at = [&](int64_t d) { return cols * ((g.nz + d - 1) / d); };
+    const auto cost_at = [&](int64_t d) { return (tiles_at(d) + cus - 1) / cus * (d + 4); };
+    // depths from the deepest; chunks of equal depth but for the last
+    const int64_t shortest = std::min<int64_t>(8, g.nz);
+    int64_t cheapest = cost_at(g.nz);
+    for (int64_t d = shortest; d < g.nz; d++) cheapest = std::min(cheapest, cost_at(d));
+    const int64_t limit = fp64 ? cheapest : cheapest + cheapest / 8;
+    int64_t depth = g.nz;
+    for (int64_t c = 1; cost_at(depth) > limit; c++) depth = std::max(shortest, (g.nz + c - 1) / c);
+    const int64_t tiles = tiles_at(depth), rounds = (tiles + cus - 1) / cus;
+    if (20 * tiles < 19 * rounds * cus) {
+        const double plane = fp64 ? 2.95 : cached ? 2.4 : 2.8;
+        const double node = (fp64 ? (cached ? 0.060 : 0.077) : (cached ? 0.025 : 0.039)) * 256.0 / cus;
+        const double untiled = node * 1e-3 * BLOCK_T * block_grid(g).count;
+        if (untiled < plane * (double)(rounds * (depth + 4))) return t;
     }
-    if (4 * best_tiles < 3 * cus) return t;  // untiled
     t.by = by;
-    t.tz = best_tz;
+    t.tz = (int)depth;
     return t;
 }
 
