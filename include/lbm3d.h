@@ -175,10 +175,12 @@ int32_t lbm3d_get_tile(lbm3d_t h, int32_t* by, int32_t* tz);
 /* Store kind of the tiled kernels' new level: 1 = non-temporal (streaming
  * past the caches), 0 = plain.  A solve starts with plain stores when its
  * two distribution levels fit in 320 MiB (the next step then reads much of
- * its input from the 256 MB memory-side cache), else with non-temporal
- * ones; the autotuner picks it with the shape.  Results are bitwise
- * independent of it; the untiled kernel always stores plainly and the
- * batched step non-temporally.  E_INVAL for a value other than 0 or 1. */
+ * its input from the 256 MB memory-side cache) or its rows end inside a
+ * cache line (nx not a multiple of 64; in FP64 only above 640 MiB), else
+ * with non-temporal ones; the autotuner picks it with the shape.  Results
+ * are bitwise independent of it; the untiled kernel always stores plainly
+ * and the batched step follows its members' levels together.  E_INVAL for a
+ * value other than 0 or 1. */
 int32_t lbm3d_set_streaming(lbm3d_t h, int32_t streaming);
 int32_t lbm3d_get_streaming(lbm3d_t h, int32_t* streaming);
 

@@ -1,6 +1,6 @@
-// Batched stepping: many solves of uneven size advanced by one persistent
-// launch per step over per-XCD tile lists, with step runs replayed from a
-// captured HIP graph.
+// Batched stepping: many solves of uneven size advanced group by group, a
+// step of a group one launch (persistent, over per-XCD tile lists, or of
+// untiled blocks), with step runs replayed from captured HIP graphs.
 #include "lbm3d_batch.h"
 
 #include <algorithm>

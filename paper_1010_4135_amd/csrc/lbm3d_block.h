@@ -11,7 +11,8 @@
 //    then come from LDS;
 //  - 32 x 8 nodes: a smaller halo than 64 x 4 and whole 128-byte rows.
 //    Measured per step against 16 x 16 blocks: 64^3 FP32 10.1 / 12.1 us,
-//    96x64x64 bubble FP32 with FP64 moments 17.5 / 20.1, 32^3 5.1 / 5.4;
+//    96x64x64 bubble FP32 with FP64 moments 17.5 / 20.1 (before the face
+//    blocks were spread over the shader engines: 16.7), 32^3 5.1 / 5.4;
 //  - the z terms are reduced to a difference and a Laplacian part per
 //    velocity before the moments, which keeps the FP32 modes at four
 //    wavefronts per SIMD without a spill (FP64: two; capping it at three
@@ -19,15 +20,17 @@
 //  - boundary layers need neither memory nor a launch of their own: periodic
 //    neighbours are addressed on the other side, fixed states are read (they
 //    never change), and the layers of extrapolating and reflecting faces are
-//    formed by the wavefronts that use them from the moments of the two
-//    nodes next to the face, with layer_line's operations, so results are
-//    bitwise those of layers kept in memory.  Blocks away from such faces
-//    skip that code.
+//    formed from the moments of the two nodes next to the face, with
+//    layer_line's operations, so results are bitwise those of layers kept in
+//    memory: those of z faces by each thread for its column, those of x and
+//    y faces once a block, by wavefronts 0 (low y), 1 (high y) and 3 (x),
+//    which leave them in the LDS halo.  Blocks away from such faces skip
+//    that code.
 // Time per step, before (one node per thread with every neighbour from
 // global memory, and a boundary-layer launch of 4 - 6 us) and now, replayed
 // from graphs: 32^3 periodic FP32 with FP64 moments 10.9 / 5.1 us; 64^3
 // periodic FP32 15.6 / 10.1; 96x64x64 bubble FP32 with FP64 moments 24.4 /
-// 17.5; 48x32x32 bubble FP64 14.4 / 9.4; 256x4x4 tube FP64 12.6 / 7.3.  An
+// 16.7; 48x32x32 bubble FP64 14.4 / 9.4; 256x4x4 tube FP64 12.6 / 7.3.  An
 // empty kernel of the same grid takes 1.8 - 2.2 us.
 #pragma once
 

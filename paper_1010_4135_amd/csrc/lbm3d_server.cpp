@@ -1,7 +1,7 @@
 // Continuous-batching server: a worker thread admits queued solves while
 // their device footprint fits the budget and a slot is free, keeps their
 // state resident on the device, advances all active solves together in
-// batched ticks (one persistent launch per step per precision group), and
+// batched ticks (one plan of the batched step per precision), and
 // completes each ticket when its solve has done its steps.  A helper thread
 // does the host work of admitting (create, upload, initialise) and of
 // completing (read back) while the ticks run.

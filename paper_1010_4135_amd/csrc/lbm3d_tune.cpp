@@ -59,6 +59,15 @@ std::vector<TileCfg> tile_candidates(int mode, const Grid& g)
                 if (tz > 2 * std::max(g.nz, 1) && tz != tzs[0]) continue;  // deeper than the grid adds nothing
                 if (tile_supported(mode, g, t)) c.push_back(t);
             }
+    // the launch model's shape, whose depth may be any: 160^3 FP32 takes 123
+    // us with its 40 planes and 157 with the best of the depths above
+    TileCfg model = default_tile(mode, g);
+    bool listed = model.by == 0;
+    for (const TileCfg& t : c) listed = listed || (t.by == model.by && t.tz == model.tz);
+    for (bool stream : {true, false}) {
+        model.stream = stream;
+        if (!listed) c.push_back(model);
+    }
     return c;
 }
 
