@@ -139,10 +139,9 @@ void BatchPlan::release_graphs()
     groups_.clear();
 }
 
-// Planes the busiest compute unit marches when the tiles of a membership at
-// depth d are dealt out longest first, each to the unit that is free first
-// (as the persistent workgroups take them): each tile its planes plus the
-// ones its z ring loads first.
+// The least planes the busiest compute unit can march when the tiles of a
+// membership at depth d are dealt out longest first, each to the unit that is
+// free first: each tile its planes plus the ones its z ring loads first.
 static double tile_makespan(const std::vector<Grid>& grids, int by, int d, int cus)
 {
     std::map<int, int64_t, std::greater<int>> tiles;  // by depth
@@ -177,25 +176,60 @@ static double tile_makespan(const std::vector<Grid>& grids, int by, int d, int c
     return last;
 }
 
+// Planes the busiest workgroup of a plan marches: the workgroups of a list
+// take its tiles in order, each when it is free.  A list that holds one more
+// deep tile than it has workgroups takes a whole tile longer than tile_makespan
+// has it (a 192x128x128 solve and three of 40^3, FP32 with FP64 moments: tiles
+// of 32 planes are 222 in all, but one list gets 32 of them for its 27
+// workgroups; 210 us a step, and 135 with the 16 planes this picks).
+static double plan_makespan(const TilePlan& p)
+{
+    double last = 0.0;
+    std::vector<double> load;  // a heap, the workgroup that is free first on top
+    for (int l = 0; l < p.nlists; l++) {
+        load.assign((size_t)(p.nblocks / p.nlists), 0.0);
+        for (int32_t j = p.queue.first[l]; j < p.queue.first[l + 1]; j++) {
+            std::pop_heap(load.begin(), load.end(), std::greater<double>());
+            load.back() += p.tiles[(size_t)j].z1 - p.tiles[(size_t)j].z0 + TILE_PROLOGUE_PLANES;
+            last = std::max(last, load.back());
+            std::push_heap(load.begin(), load.end(), std::greater<double>());
+        }
+    }
+    return last;
+}
+static double plan_makespan(const std::vector<Grid>& grids, int by, int d, int cus)
+{
+    TilePlan p;
+    // (a plan of more tiles than can be counted is refused when it is built)
+    return plan_tiles(grids, by, d, cus, p) == LBM3D_OK ? plan_makespan(p) : tile_makespan(grids, by, d, cus);
+}
+
 // Tile depth of a membership: of 16, 32, ... up to whole columns, the
-// deepest whose makespan is within 5% of the shortest: whole columns for a
-// batch as large as the 64-solve mix (as the tuner finds), short chunks for
-// a few solves, whose whole columns would leave most compute units idle.
+// deepest whose plan's makespan is within 5% of the shortest: whole columns
+// for a batch as large as the 64-solve mix (as the tuner finds), short chunks
+// for a few solves, whose whole columns would leave most compute units idle.
+// Plans are made for the depths that can be among those only.
 static int model_depth(const std::vector<Grid>& grids, int by, int cus)
 {
     int maxnz = 1;
     for (const Grid& g : grids) maxnz = std::max(maxnz, g.nz);
-    std::vector<std::pair<int, double>> tried;
-    double best = 0.0;
+    std::vector<std::pair<double, int>> least;  // makespan at best, depth
     for (int d = 16;; d *= 2) {
         const int dd = std::min(d, maxnz);
-        tried.emplace_back(dd, tile_makespan(grids, by, dd, cus));
-        if (tried.size() == 1 || tried.back().second < best) best = tried.back().second;
+        least.emplace_back(tile_makespan(grids, by, dd, cus), dd);
         if (dd >= maxnz) break;
     }
-    int depth = maxnz;
+    std::sort(least.begin(), least.end());
+    std::vector<std::pair<double, int>> tried;
+    double best = 0.0;
+    for (const auto& c : least) {
+        if (!tried.empty() && c.first > 1.05 * best) break;
+        tried.emplace_back(plan_makespan(grids, by, c.second, cus), c.second);
+        best = tried.size() == 1 ? tried[0].first : std::min(best, tried.back().first);
+    }
+    int depth = 0;
     for (const auto& t : tried)
-        if (t.second <= 1.05 * best) depth = t.first;
+        if (t.first <= 1.05 * best) depth = std::max(depth, t.second);
     return depth;
 }
 
@@ -276,7 +310,7 @@ static double tiled_us(int mode, const std::vector<lbm3d_solver*>& members, int 
         grids.push_back(h->g);
         layers = layers || ghost_faces(h->g, h->bc, true) != 0;
     }
-    return tile_makespan(grids, by, plan_depth(mode, tz, grids, by, cus), cus) * (mode == LBM3D_FP64 ? 3.3 : 3.1) +
+    return plan_makespan(grids, by, plan_depth(mode, tz, grids, by, cus), cus) * (mode == LBM3D_FP64 ? 3.3 : 3.1) +
            (layers ? 9.0 : 3.0);
 }
 static double blocks_us(int mode, const std::vector<lbm3d_solver*>& members, const GroupMembers& part, int cus)
