@@ -353,6 +353,14 @@ int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const int64_t* nste
 int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* ntiles,
                          int32_t* nlists, int32_t* nblocks, int32_t* tiles, int64_t cap, int32_t* list_first);
 
+/* How the batched step takes these solves, computed on the host (no device
+ * work; arguments and errors as lbm3d_batch_plan): group[k] receives the
+ * number of the group solve k is stepped in (groups run one after the
+ * other), tiled[k] 1 if that group goes by the tiled kernel and 0 if by the
+ * untiled kernel's blocks.  E_INVAL also if either is NULL. */
+int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
+                           int32_t* tiled);
+
 /* Autotuner of the batched step: times the persistent launch over the given
  * solves (same rules as lbm3d_batch_step) for tile depths 16, 32, 64 and 128
  * (a depth at or beyond a solve's nz gives whole columns), over `launches`
@@ -370,8 +378,9 @@ int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int3
 int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches, int32_t* tz);
 
 /* Tile depth of later batched steps (lbm3d_batch_step) of one precision
- * in this process, as the autotuner would set it; 0 restores the default
- * (the launch model's depth for each batch).  Results do not depend on it.
+ * in this process: every member of a batch then goes by tiles of that depth,
+ * also one that would go by blocks; 0 restores the default (groups, and the
+ * launch model's depth for the tiles).  Results do not depend on it.
  * E_INVAL for a bad precision or tz outside [0, 65535]. */
 int32_t lbm3d_batch_set_depth(int32_t precision, int32_t tz);
 

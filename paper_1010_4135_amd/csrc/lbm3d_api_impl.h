@@ -73,8 +73,10 @@ constexpr double STABILITY_TOL = 1e-3;
 int32_t admission(const lbm3d_params* p, const double* rho, const double* ux, const double* uy, const double* uz,
                   const double* pr, double* worst);
 // autotuner results (lbm3d_tune.cpp): the tuned tile of a solve shape, and
-// the tuned batch tile depth of a precision (0 if not tuned)
+// the set or tuned batch tile depth of a precision (0 if there is none), and
+// whether it was set (lbm3d_batch_set_depth)
 bool cached_tile(int mode, const Grid& g, const FaceBC& bc, TileCfg* out);
 int batch_tile_depth(int mode);
+bool batch_depth_set(int mode);
 
 }  // namespace lbm3d

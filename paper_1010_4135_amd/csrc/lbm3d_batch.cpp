@@ -262,20 +262,15 @@ static int plan_depth(int mode, int tz, const std::vector<Grid>& grids, int by, 
 // 150).
 constexpr int64_t GROUP_BYTES = (int64_t)192 << 20, ALONE_BYTES = (int64_t)256 << 20;
 
-struct GroupMembers {
-    std::vector<int32_t> who;
-    int64_t bytes = 0;
-    bool tiled = false;
-};
-
-static std::vector<GroupMembers> group_members(const std::vector<lbm3d_solver*>& members)
+static std::vector<GroupMembers> group_members(int mode, const std::vector<BatchMember>& members)
 {
     std::vector<GroupMembers> out;
     GroupMembers large;
     large.tiled = true;
     std::vector<std::pair<int64_t, int32_t>> fits;
     for (size_t k = 0; k < members.size(); k++) {
-        const int64_t b = members[k]->n * 2 * NV * (int64_t)elem_size(members[k]->mode);
+        const Grid& g = members[k].g;
+        const int64_t b = (int64_t)g.nx * g.ny * g.nz * 2 * NV * (int64_t)elem_size(mode);
         if (b > ALONE_BYTES)
             large.who.push_back((int32_t)k);
         else
@@ -302,36 +297,37 @@ static std::vector<GroupMembers> group_members(const std::vector<lbm3d_solver*>&
 // Time of a step of tiled members or of one untiled group, from what the
 // headline solve and the groups above measured per plane of a tile and per
 // block (at 256 compute units), with their launches.
-static double tiled_us(int mode, const std::vector<lbm3d_solver*>& members, int tz, int by, int cus)
+static double tiled_us(int mode, const std::vector<BatchMember>& members, int tz, int by, int cus)
 {
     std::vector<Grid> grids;
     bool layers = false;
-    for (const lbm3d_solver* h : members) {
-        grids.push_back(h->g);
-        layers = layers || ghost_faces(h->g, h->bc, true) != 0;
+    for (const BatchMember& m : members) {
+        grids.push_back(m.g);
+        layers = layers || ghost_faces(m.g, m.bc, true) != 0;
     }
     return plan_makespan(grids, by, plan_depth(mode, tz, grids, by, cus), cus) * (mode == LBM3D_FP64 ? 3.3 : 3.1) +
            (layers ? 9.0 : 3.0);
 }
-static double blocks_us(int mode, const std::vector<lbm3d_solver*>& members, const GroupMembers& part, int cus)
+static double blocks_us(int mode, const std::vector<BatchMember>& members, const GroupMembers& part, int cus)
 {
     double blocks = 0.0;
-    for (int32_t k : part.who) blocks += block_grid(members[(size_t)k]->g).count;
+    for (int32_t k : part.who) blocks += block_grid(members[(size_t)k].g).count;
     return 2.5 + blocks * (mode == LBM3D_FP64 ? 0.017 : 0.007) * 256.0 / cus;
 }
 
-// The groups of a plan: as group_members has them, or all members tiled.
-static std::vector<GroupMembers> plan_groups(const std::vector<lbm3d_solver*>& members, int tz, int by, int cus)
+std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& members, int tz, int cus)
 {
-    std::vector<GroupMembers> parts = group_members(members);
-    const int mode = members[0]->mode;
-    double apart = 0.0;
-    for (const GroupMembers& part : parts) {
-        std::vector<lbm3d_solver*> mine;
-        for (int32_t k : part.who) mine.push_back(members[(size_t)k]);
-        apart += part.tiled ? tiled_us(mode, mine, tz, by, cus) : blocks_us(mode, members, part, cus);
+    const int by = mode == LBM3D_FP64 ? 4 : 8;
+    if (tz <= 0 && !(tz == 0 && batch_depth_set(mode))) {
+        const std::vector<GroupMembers> parts = group_members(mode, members);
+        double apart = 0.0;
+        for (const GroupMembers& part : parts) {
+            std::vector<BatchMember> mine;
+            for (int32_t k : part.who) mine.push_back(members[(size_t)k]);
+            apart += part.tiled ? tiled_us(mode, mine, tz, by, cus) : blocks_us(mode, members, part, cus);
+        }
+        if (apart <= tiled_us(mode, members, tz, by, cus)) return parts;
     }
-    if (apart <= tiled_us(mode, members, tz, by, cus)) return parts;
     GroupMembers all;
     all.tiled = true;
     for (size_t k = 0; k < members.size(); k++) all.who.push_back((int32_t)k);
@@ -339,14 +335,14 @@ static std::vector<GroupMembers> plan_groups(const std::vector<lbm3d_solver*>& m
 }
 
 // layer jobs of tiled members (faces the tiles leave to memory)
-static void layer_jobs(const std::vector<lbm3d_solver*>& members, std::vector<BatchLayerJob>& ljobs,
+static void layer_jobs(const std::vector<BatchMember>& members, std::vector<BatchLayerJob>& ljobs,
                        std::vector<int32_t>& block_job, int& nlblocks)
 {
     ljobs.clear();
     nlblocks = 0;
     for (size_t k = 0; k < members.size(); k++) {
-        const Grid& g = members[k]->g;
-        const uint32_t faces = ghost_faces(g, members[k]->bc, true);
+        const Grid& g = members[k].g;
+        const uint32_t faces = ghost_faces(g, members[k].bc, true);
         if (!faces) continue;
         int64_t lines = 0;
         for (int face = 0; face < 6; face++) {
@@ -382,14 +378,18 @@ size_t BatchPlan::table_bytes(const std::vector<lbm3d_solver*>& members, int tz)
     const int mode = members[0]->mode;
     const int by = mode == LBM3D_FP64 ? 4 : 8;
     std::vector<Grid> grids;
-    for (lbm3d_solver* h : members) grids.push_back(h->g);
+    std::vector<BatchMember> all;
+    for (lbm3d_solver* h : members) {
+        grids.push_back(h->g);
+        all.push_back(BatchMember{h->g, h->bc});
+    }
     TilePlan p;
     const int cus = device_cus();
     if (plan_tiles(grids, by, plan_depth(mode, tz, grids, by, cus), cus, p) != LBM3D_OK) return (size_t)-1;
     std::vector<BatchLayerJob> lj;
     std::vector<int32_t> bj;
     int nlb = 0;
-    layer_jobs(members, lj, bj, nlb);
+    layer_jobs(all, lj, bj, nlb);
     return tables_need(members.size(), p.tiles.size(), lj.size(), (size_t)nlb);
 }
 
@@ -416,7 +416,9 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         image.resize(at + bytes, 0);
         return at;
     };
-    const std::vector<GroupMembers> parts = plan_groups(members, tz, by_, cus);
+    std::vector<BatchMember> shapes;
+    for (lbm3d_solver* h : members) shapes.push_back(BatchMember{h->g, h->bc});
+    const std::vector<GroupMembers> parts = plan_groups(mode_, shapes, tz, cus);
     const size_t solves_at = place(members.size() * sizeof(BatchSolve));
     const size_t health_at = place(members.size() * sizeof(uint32_t));
     struct Offsets {
@@ -428,11 +430,11 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         q.first = (int)members_.size();
         q.n = (int)part.who.size();
         q.tiled = part.tiled;
-        std::vector<lbm3d_solver*> mine;
+        std::vector<BatchMember> mine;
         for (int32_t k : part.who) {
             members_.push_back(members[(size_t)k]);
             order_.push_back(k);
-            mine.push_back(members[(size_t)k]);
+            mine.push_back(shapes[(size_t)k]);
         }
         Offsets o{};
         o.queue = place(sizeof(BatchQueue));
@@ -441,11 +443,11 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         if (part.tiled) {
             std::vector<Grid> grids;
             int64_t level_bytes = 0, dense_bytes = 0;
-            for (lbm3d_solver* h : mine) {
-                grids.push_back(h->g);
-                const int64_t bytes = 2 * (int64_t)f_bytes(h->g, h->mode);
+            for (const BatchMember& m : mine) {
+                grids.push_back(m.g);
+                const int64_t bytes = 2 * (int64_t)f_bytes(m.g, mode_);
                 level_bytes += bytes;
-                if (dense_rows(h->g.nx) || mode_ == LBM3D_FP64) dense_bytes += bytes;
+                if (dense_rows(m.g.nx) || mode_ == LBM3D_FP64) dense_bytes += bytes;
             }
             // plain stores when the levels together fit the memory-side
             // cache, or most of them have rows that end inside a cache
@@ -474,7 +476,7 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         } else {
             o.grids = place(mine.size() * sizeof(BlockGrid));
             for (size_t k = 0; k < mine.size(); k++) {
-                const BlockGrid bg = block_grid(mine[k]->g);
+                const BlockGrid bg = block_grid(mine[k].g);
                 std::memcpy(image.data() + o.grids + k * sizeof(BlockGrid), &bg, sizeof(BlockGrid));
                 const int first = q.nblocks;
                 for (uint32_t b = 0; b < bg.count; b += BATCH_BLOCKS) {
@@ -838,5 +840,29 @@ extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32
             o[6] = t.z1;
         }
     }
+    return LBM3D_OK;
+}
+
+extern "C" int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
+                                      int32_t* tiled)
+{
+    if (!ps || count < 1 || cus < 1 || !group || !tiled) return LBM3D_E_INVAL;
+    std::vector<BatchMember> members;
+    for (int32_t k = 0; k < count; k++) {
+        int32_t rc = validate(&ps[k]);
+        if (rc) return rc;
+        if (ps[k].precision != ps[0].precision || (ps[k].flags & LBM3D_UPWIND2)) return LBM3D_E_INVAL;
+        BatchMember m;
+        m.g = make_grid(&ps[k]);
+        if (!tiled_fits(ps[k].precision, m.g)) return LBM3D_E_INVAL;
+        for (int f = 0; f < 6; f++) m.bc.kind[f] = ps[k].bc[f];
+        members.push_back(m);
+    }
+    const std::vector<GroupMembers> parts = plan_groups(ps[0].precision, members, tz, cus);
+    for (size_t j = 0; j < parts.size(); j++)
+        for (int32_t k : parts[j].who) {
+            group[k] = (int32_t)j;
+            tiled[k] = parts[j].tiled ? 1 : 0;
+        }
     return LBM3D_OK;
 }

@@ -24,8 +24,27 @@ struct TilePlan {
 // list runs its deepest tiles first.  Host only.
 int32_t plan_tiles(const std::vector<Grid>& grids, int by, int tz, int cus, TilePlan& out);
 
+// What the plan of a batch depends on of a member.
+struct BatchMember {
+    Grid g;
+    FaceBC bc;
+};
+// Members stepped by one launch (their places in the membership), by the
+// tiled kernel or by untiled blocks.
+struct GroupMembers {
+    std::vector<int32_t> who;
+    int64_t bytes = 0;
+    bool tiled = false;
+};
+// The groups of a plan at tile depth tz (as for BatchPlan::build): all members
+// tiled in one group where the caller asks for a depth (tz > 0, or the
+// precision's was set by lbm3d_batch_set_depth), or where a model of both
+// kernels finds that the faster; else cache-sized groups of untiled blocks and
+// one of the larger members, tiled.  Host only.
+std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& members, int tz, int cus);
+
 // A fixed set of solves (one precision) advanced together, group by group
-// (see group_members): a device table of the solves, the work items of each
+// (see plan_groups): a device table of the solves, the work items of each
 // group and one launch per step and group (and one for the boundary layers
 // tiles leave to memory); runs of steps are replayed from captured graphs.
 class BatchPlan {
@@ -37,8 +56,8 @@ public:
 
     // (Re)build for `members` (all initialised, same precision); each
     // member's current buffer is taken as parity 0.  Enqueued on `s`.
-    // `tz` > 0 sets the tile depth; 0 takes the tuned depth of the
-    // precision, else the launch model's; < 0 the launch model's.
+    // `tz` > 0 sets the tile depth of every member; 0 takes the set or tuned
+    // depth of the precision, else the launch model's; < 0 the launch model's.
     // The device tables go into a buffer the plan allocates, or, with
     // `dev` != nullptr, into the caller's `cap` bytes at `dev` (then nothing
     // is allocated and E_NOMEM is returned if they do not fit).

@@ -38,7 +38,8 @@ ShapeKey key_of(int mode, const Grid& g, const FaceBC& bc)
 
 std::mutex g_mu;
 std::map<ShapeKey, TileCfg> g_tiles;  // tuned tile per solve shape
-int g_batch_tz[3] = {0, 0, 0};        // tuned batch tile depth per precision (0: not tuned)
+int g_batch_tz[3] = {0, 0, 0};        // set or tuned batch tile depth per precision (0: neither)
+bool g_batch_set[3] = {};             // it was set: every member of a batch goes tiled
 
 std::vector<TileCfg> tile_candidates(int mode, const Grid& g)
 {
@@ -145,7 +146,10 @@ int32_t load_locked(const char* path)
     if (!ok) return LBM3D_E_INVAL;  // nothing merged from a bad file
     for (const auto& kv : tiles) g_tiles[kv.first] = kv.second;
     for (int m = 0; m < 3; m++)
-        if (batch[m] > 0) g_batch_tz[m] = batch[m];
+        if (batch[m] > 0) {
+            g_batch_tz[m] = batch[m];
+            g_batch_set[m] = false;
+        }
     return LBM3D_OK;
 }
 
@@ -177,6 +181,12 @@ int batch_tile_depth(int mode)
     std::lock_guard<std::mutex> lk(g_mu);
     env_load_locked();
     return (mode >= 0 && mode < 3) ? g_batch_tz[mode] : 0;
+}
+
+bool batch_depth_set(int mode)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    return mode >= 0 && mode < 3 && g_batch_set[mode];
 }
 
 }  // namespace lbm3d
@@ -299,6 +309,7 @@ extern "C" int32_t lbm3d_batch_set_depth(int32_t precision, int32_t tz)
     std::lock_guard<std::mutex> lk(g_mu);
     env_load_locked();
     g_batch_tz[precision] = tz;
+    g_batch_set[precision] = tz > 0;
     return LBM3D_OK;
 }
 
@@ -390,6 +401,7 @@ extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches
         std::lock_guard<std::mutex> lk(g_mu);
         env_load_locked();
         g_batch_tz[hs[0]->mode] = best_tz;
+        g_batch_set[hs[0]->mode] = false;
         if (const char* p = env_cache()) (void)save_locked(p);
     }
     if (tz) *tz = best_tz;

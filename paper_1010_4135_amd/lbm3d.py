@@ -101,6 +101,7 @@ def _load():
         "lbm3d_batch_step_noalloc": (I32, [ctypes.POINTER(P), I32, ctypes.POINTER(I64)]),
         "lbm3d_batch_plan": (I32, [PP, I32, I32, I32, ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32),
                                    ctypes.POINTER(I32), I64, ctypes.POINTER(I32)]),
+        "lbm3d_batch_groups": (I32, [PP, I32, I32, I32, ctypes.POINTER(I32), ctypes.POINTER(I32)]),
         "lbm3d_server_create": (I32, [SZ, I32, ctypes.POINTER(P)]),
         "lbm3d_server_set_tick": (I32, [P, I64]),
         "lbm3d_server_submit": (I32, [P, PP, D, D, D, D, D, I64, ctypes.POINTER(U64)]),
@@ -367,6 +368,16 @@ def lbm3d_batch_plan(params_list, tz: int = 0, cus: int = 256):
                                  tiles.ctypes.data_as(I32P), tiles.shape[0], first.ctypes.data_as(I32P)),
            "lbm3d_batch_plan")
     return tiles[:nt.value], first[:nl.value + 1], nb.value
+
+
+def lbm3d_batch_groups(params_list, tz: int = 0, cus: int = 256):
+    """Host-side grouping of the batched step: (group, tiled), the number of
+    each solve's group and whether that group goes by the tiled kernel."""
+    n = len(params_list)
+    arr = (lbm3d_params * n)(*[_params(p) for p in params_list])
+    group, tiled = (ctypes.c_int32 * n)(), (ctypes.c_int32 * n)()
+    _check(_lib.lbm3d_batch_groups(arr, n, int(tz), int(cus), group, tiled), "lbm3d_batch_groups")
+    return list(group), [bool(t) for t in tiled]
 
 
 def lbm3d_batch_tune(handles, launches: int = 5) -> int:
