@@ -361,15 +361,18 @@ int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int3
 int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
                            int32_t* tiled);
 
-/* Autotuner of the batched step: times the persistent launch over the given
- * solves (same rules as lbm3d_batch_step) for tile depths 16, 32, 64 and 128
+/* Autotuner of the batched step: times the persistent launch over those of
+ * the given solves (same rules as lbm3d_batch_step) that a batch of them
+ * steps by tiles (see lbm3d_batch_groups) for tile depths 16, 32, 64 and 128
  * (a depth at or beyond a solve's nz gives whole columns), over `launches`
  * steps each (<= 0: 5) in three interleaved rounds, as real steps over
  * alternating buffers with the solves' current levels and health words
  * saved to temporary device memory and restored afterwards (states
  * unchanged; without memory for the copies each trial recomputes the
- * current levels), and keeps the depth with the fastest round for every later batched
- * step (lbm3d_batch_step) of that precision in this process.  Servers do
+ * current levels), and keeps the depth with the fastest round for the tiles
+ * of every later batched step (lbm3d_batch_step) of that precision in this
+ * process.  If all of them go by blocks, which have no depth, nothing is
+ * timed or kept and *tz receives the launch model's depth.  Servers do
  * not use it: their membership changes from tick to tick, and each of
  * their plans takes the launch model's depth for its members (the
  * persistent workgroups share the tiles' planes, and no launch ends before

@@ -334,6 +334,13 @@ std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& 
     return {all};
 }
 
+int batch_model_depth(int mode, const std::vector<BatchMember>& members, int cus)
+{
+    std::vector<Grid> grids;
+    for (const BatchMember& m : members) grids.push_back(m.g);
+    return model_depth(grids, mode == LBM3D_FP64 ? 4 : 8, cus);
+}
+
 // layer jobs of tiled members (faces the tiles leave to memory)
 static void layer_jobs(const std::vector<BatchMember>& members, std::vector<BatchLayerJob>& ljobs,
                        std::vector<int32_t>& block_job, int& nlblocks)

@@ -42,6 +42,8 @@ struct GroupMembers {
 // kernels finds that the faster; else cache-sized groups of untiled blocks and
 // one of the larger members, tiled.  Host only.
 std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& members, int tz, int cus);
+// The launch model's depth for these members, were they all tiled.
+int batch_model_depth(int mode, const std::vector<BatchMember>& members, int cus);
 
 // A fixed set of solves (one precision) advanced together, group by group
 // (see plan_groups): a device table of the solves, the work items of each

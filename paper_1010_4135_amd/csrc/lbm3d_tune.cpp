@@ -321,7 +321,19 @@ extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches
     hipStream_t s = hs[0]->stream;
     for (int32_t k = 0; k < count; k++)
         if (hipStreamSynchronize(hs[k]->stream) != hipSuccess) return LBM3D_E_DEVICE;
-    std::vector<lbm3d_solver*> members(hs, hs + count);
+    // Only the members that a batch of these steps by tiles are timed: blocks
+    // have no depth.  Without such members there is nothing to choose.
+    std::vector<BatchMember> shapes;
+    for (int32_t k = 0; k < count; k++) shapes.push_back(BatchMember{hs[k]->g, hs[k]->bc});
+    std::vector<lbm3d_solver*> members;
+    for (const GroupMembers& part : plan_groups(hs[0]->mode, shapes, -1, device_cus()))
+        for (int32_t k : part.who)
+            if (part.tiled) members.push_back(hs[k]);
+    if (members.empty()) {
+        if (tz) *tz = batch_model_depth(hs[0]->mode, shapes, device_cus());
+        return LBM3D_OK;
+    }
+    const int n = (int)members.size();
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -341,19 +353,19 @@ extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches
     // members' current buffers and health words are saved first and
     // restored afterwards.  Without device memory for the copies the trials
     // recompute the current level.
-    std::vector<size_t> off(count + 1, 0);
-    for (int32_t k = 0; k < count; k++) off[k + 1] = off[k] + f_bytes(hs[k]->g, hs[k]->mode);
+    std::vector<size_t> off(n + 1, 0);
+    for (int k = 0; k < n; k++) off[k + 1] = off[k] + f_bytes(members[k]->g, members[k]->mode);
     char* backup = nullptr;
-    if (e == hipSuccess && hipMalloc((void**)&backup, off[count]) != hipSuccess) {
+    if (e == hipSuccess && hipMalloc((void**)&backup, off[n]) != hipSuccess) {
         (void)hipGetLastError();
         backup = nullptr;
     }
-    std::vector<uint32_t> health0(count, 0u);
-    for (int32_t k = 0; k < count && e == hipSuccess; k++) {
+    std::vector<uint32_t> health0(n, 0u);
+    for (int k = 0; k < n && e == hipSuccess; k++) {
         if (backup)
-            e = hipMemcpyAsync(backup + off[k], hs[k]->f[hs[k]->cur], off[k + 1] - off[k], hipMemcpyDeviceToDevice, s);
+            e = hipMemcpyAsync(backup + off[k], members[k]->f[members[k]->cur], off[k + 1] - off[k], hipMemcpyDeviceToDevice, s);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(&health0[k], hs[k]->health, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
+            e = hipMemcpyAsync(&health0[k], members[k]->health, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     // interleaved rounds, each depth keeping its fastest (as for the tiles)
@@ -378,11 +390,11 @@ extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches
     }
     // restore the members' current levels and health words (also after an error)
     hipError_t e2 = hipSuccess;
-    for (int32_t k = 0; k < count && e2 == hipSuccess; k++) {
+    for (int k = 0; k < n && e2 == hipSuccess; k++) {
         if (backup)
-            e2 = hipMemcpyAsync(hs[k]->f[hs[k]->cur], backup + off[k], off[k + 1] - off[k], hipMemcpyDeviceToDevice, s);
+            e2 = hipMemcpyAsync(members[k]->f[members[k]->cur], backup + off[k], off[k + 1] - off[k], hipMemcpyDeviceToDevice, s);
         if (e2 == hipSuccess)
-            e2 = hipMemcpyAsync(hs[k]->health, &health0[k], sizeof(uint32_t), hipMemcpyHostToDevice, s);
+            e2 = hipMemcpyAsync(members[k]->health, &health0[k], sizeof(uint32_t), hipMemcpyHostToDevice, s);
     }
     if (e2 == hipSuccess) e2 = hipStreamSynchronize(s);
     if (backup) (void)hipFree(backup);
