@@ -125,25 +125,52 @@ size_t footprint_of(const lbm3d_params* p)
 
 // ------------------------------------------------------------- host copies --
 // Fields come from and go to pageable memory of the caller.  The runtime
-// copies that through its own pinned buffer with one thread, whose page
-// faults (in fresh memory) and memcpy hold the transfer to 7 - 10 GB/s; here
-// several threads each move chunks through a slot of a pinned buffer of the
-// library.  Reading back the five fields of a 256x128x128 solve (168 MB)
-// takes 4.9 ms instead of 17.7, those of 256^3 (671 MB) 16 instead of 66.
-// Slots of 4 MiB: with 1 MiB those are 6.2 and 23.  Smaller transfers are cut
-// into one chunk per thread, and the buffer is no larger than they need,
-// since pinning it takes about 0.1 ms per MiB.
+// copies that through its own pinned buffer with one thread, whose memcpy and,
+// in fresh memory, page faults hold the transfer to 8 - 18 GB/s; here several
+// threads each move chunks through a slot of a pinned buffer of the library.
+// Reading back the five fields of a 128^3 solve (84 MB) takes 2.1 ms instead
+// of 4.7, an FP64 state of it (252 MB, fresh memory) 14 instead of 27.
 namespace lbm3d {
 
-constexpr unsigned COPY_THREADS = 8;
-constexpr size_t COPY_CHUNK = (size_t)4 << 20;     // largest slot, bytes
-constexpr size_t COPY_HOST_CHUNK = (size_t)1 << 20;
-// Below these, one thread and the runtime's own path.  To the host, page
-// faults of fresh memory make it the slower one from the start (10 MB 0.68 ms
-// against 0.45); from it, the runtime stages small copies at 30 GB/s (16 MB
-// 0.52 ms against 0.66, 24 MB 0.81 against 0.93) and large ones at 8 (126 MB
-// 15.6 ms against 5.9).
-constexpr size_t COPY_MIN = (size_t)2 << 20, COPY_MIN_UP = (size_t)32 << 20;
+constexpr unsigned COPY_THREADS = 8, COPY_FEW = 3;
+constexpr size_t COPY_SLOT = (size_t)4 << 20, COPY_FEW_SLOT = (size_t)2 << 20;  // bytes of a slot, the largest chunk
+constexpr size_t COPY_HOST_CHUNK = (size_t)1 << 20, COPY_HOST_MIN = (size_t)2 << 20;  // copies within the host
+// Below COPY_MIN (to the host) and COPY_MIN_UP, one thread and the runtime's
+// own path: starting threads and a wait per chunk cost some 0.1 ms (3 MiB to
+// the host 0.17 - 0.20 ms either way, 5 MiB 0.22 and 0.30); from the host, the
+// runtime stages small copies at 30 GB/s (16 MB 0.52 ms against 0.66, 24 MB
+// 0.81 against 0.93) and large ones at 8 (126 MB 15.6 ms against 5.9).  From
+// COPY_MANY on a single array is memory fresh from the system, where page
+// faults need the eight threads (31 MiB: 0.90 ms with three threads and 0.91
+// with eight; 40 MiB: 4.5 and 2.7, the runtime 9.8).  Slots of 1 MiB: 16 MiB
+// 0.61 ms with three threads instead of 0.54, of 4 MiB no faster; with eight
+// threads 84 MiB 2.06 ms with 4 MiB and 2.25 with 2.
+constexpr size_t COPY_MIN = (size_t)4 << 20, COPY_MIN_UP = (size_t)32 << 20, COPY_MANY = (size_t)32 << 20;
+
+// Making the buffer costs 1.5 - 2.5 ms (its pages are faulted in), and with its
+// release the next solve's first transfers take some 3 ms longer, where a
+// transfer of 10 MiB gains 0.2 ms and one of 20 MiB 0.5.  So it is made by a
+// transfer that gains more than that by itself (COPY_MANY), or once as much
+// has gone through the runtime for want of it as would have paid for it
+// (COPY_EARN): short-lived solves do not pay for it (64^3 created, stepped,
+// read back and destroyed: 1.6 ms, and 5.3 - 6.5 with a buffer each time).
+constexpr size_t COPY_EARN = (size_t)128 << 20;
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed)
+{
+    CopyPlan p;
+    if (total < (down ? COPY_MIN : COPY_MIN_UP)) return p;
+    const bool many = total >= COPY_MANY;
+    const unsigned threads = many ? COPY_THREADS : COPY_FEW;
+    const size_t slot = many ? COPY_SLOT : COPY_FEW_SLOT;
+    p.wants = true;
+    if (buffer < threads * slot) {
+        if (!many && passed + total < COPY_EARN) return p;
+        p.make = threads * slot;
+    }
+    p.threads = threads;
+    p.chunk = std::min(((total + threads - 1) / threads + 65535) & ~(size_t)65535, slot);
+    return p;
+}
 
 // Runs work(k) for k = 0 .. chunks - 1 (none may throw) on up to COPY_THREADS
 // threads, the calling one among them: it does all that is left if no other
@@ -170,7 +197,7 @@ static void for_chunks(size_t chunks, const Work& work)
 void copy_host(double* dst, const double* src, size_t n)
 {
     constexpr size_t per = COPY_HOST_CHUNK / sizeof(double);
-    if (n * sizeof(double) < COPY_MIN) {
+    if (n * sizeof(double) < COPY_HOST_MIN) {
         std::memcpy(dst, src, n * sizeof(double));
         return;
     }
@@ -202,13 +229,13 @@ static bool bad_state(size_t n, const double* rho, const double* ux, const doubl
     return bad;
 }
 
-// The pinned buffer: COPY_THREADS slots, for one transfer at a time (another
-// one meanwhile takes the runtime's own path), allocated by the first transfer
-// that needs it, replaced by a larger one up to 32 MiB, and given back with
-// the last user.
+// The pinned buffer (6 or 32 MiB, see copy_plan), for one transfer at a time
+// (another one meanwhile takes the runtime's own path), given back with the
+// last user.
 static std::mutex g_staging_mu;       // held by the transfer that uses the buffer
 static char* g_staging = nullptr;
-static size_t g_slot = 0;             // bytes of a slot
+static size_t g_staging_bytes = 0;
+static size_t g_passed = 0;           // bytes that went through the runtime for want of the buffer
 static std::atomic<long> g_staging_users{0};
 
 void staging_ref() { g_staging_users++; }
@@ -216,11 +243,11 @@ void staging_unref()
 {
     if (--g_staging_users > 0) return;
     std::lock_guard<std::mutex> lk(g_staging_mu);
-    if (g_staging && g_staging_users == 0) {
-        (void)hipHostFree(g_staging);
-        g_staging = nullptr;
-        g_slot = 0;
-    }
+    if (g_staging_users != 0) return;
+    if (g_staging) (void)hipHostFree(g_staging);
+    g_staging = nullptr;
+    g_staging_bytes = 0;
+    g_passed = 0;
 }
 
 // Moves every chunk of the items through a slot; false (and nothing done) if
@@ -234,30 +261,33 @@ static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipEr
     };
     size_t total = 0;
     for (int i = 0; i < n; i++) total += items[i].bytes;
-    const size_t part = ((total + COPY_THREADS - 1) / COPY_THREADS + 65535) & ~(size_t)65535;
-    const size_t chunk = std::min(part, COPY_CHUNK);
-    std::vector<Chunk> chunks;
-    for (int i = 0; i < n; i++)
-        for (size_t a = 0; a < items[i].bytes; a += chunk)
-            chunks.push_back(
-                Chunk{(char*)items[i].host + a, (char*)items[i].dev + a, std::min(chunk, items[i].bytes - a)});
     std::unique_lock<std::mutex> lk(g_staging_mu, std::try_to_lock);
     if (!lk.owns_lock()) return false;
-    if (g_slot < chunk) {
+    const CopyPlan plan = copy_plan(total, down, g_staging_bytes, g_passed);
+    if (!plan.threads) {
+        if (plan.wants) g_passed += total;
+        return false;
+    }
+    std::vector<Chunk> chunks;
+    for (int i = 0; i < n; i++)
+        for (size_t a = 0; a < items[i].bytes; a += plan.chunk)
+            chunks.push_back(
+                Chunk{(char*)items[i].host + a, (char*)items[i].dev + a, std::min(plan.chunk, items[i].bytes - a)});
+    if (plan.make) {
         if (g_staging) (void)hipHostFree(g_staging);
-        g_slot = 0;
-        if (hipHostMalloc((void**)&g_staging, COPY_THREADS * chunk, hipHostMallocPortable) != hipSuccess) {
+        g_staging_bytes = 0;
+        if (hipHostMalloc((void**)&g_staging, plan.make, hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             g_staging = nullptr;
             return false;
         }
-        g_slot = chunk;
+        g_staging_bytes = plan.make;
     }
     int device = 0;
     hipError_t first = hipGetDevice(&device);
     if (first != hipSuccess) return false;
     hipEvent_t done[COPY_THREADS] = {};
-    for (unsigned t = 0; t < COPY_THREADS; t++)
+    for (unsigned t = 0; t < plan.threads; t++)
         if (hipEventCreateWithFlags(&done[t], hipEventDisableTiming) != hipSuccess) {
             (void)hipGetLastError();
             for (unsigned u = 0; u < t; u++) (void)hipEventDestroy(done[u]);
@@ -266,8 +296,8 @@ static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipEr
     std::atomic<size_t> next{0};
     std::atomic<int> error{hipSuccess};
     // one slot per worker, each chunk through it and out before the next
-    for_chunks(std::min<size_t>(COPY_THREADS, chunks.size()), [&](size_t w) {
-        char* slot = g_staging + w * g_slot;
+    for_chunks(std::min<size_t>(plan.threads, chunks.size()), [&](size_t w) {
+        char* slot = g_staging + w * plan.chunk;
         hipError_t e = hipSetDevice(device);
         for (size_t k; e == hipSuccess && error == hipSuccess && (k = next.fetch_add(1)) < chunks.size();) {
             const Chunk& c = chunks[k];
@@ -282,7 +312,7 @@ static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipEr
     });
     // (an error may leave a copy into a slot queued)
     if (error != hipSuccess) (void)hipStreamSynchronize(s);
-    for (unsigned t = 0; t < COPY_THREADS; t++) (void)hipEventDestroy(done[t]);
+    for (unsigned t = 0; t < plan.threads; t++) (void)hipEventDestroy(done[t]);
     *result = (hipError_t)error.load();
     return true;
 }

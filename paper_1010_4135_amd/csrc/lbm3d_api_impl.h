@@ -57,6 +57,17 @@ struct HostCopy {
     void* dev;
     size_t bytes;
 };
+// How a transfer of `total` bytes goes when the pinned buffer has `buffer`
+// bytes (0: there is none) and `passed` bytes have gone through the runtime
+// for want of it: by `threads` threads in chunks of `chunk` bytes, after
+// making a buffer of `make` bytes if that is not 0, or, with no threads,
+// through the runtime, `wants` saying that the buffer would have served.
+struct CopyPlan {
+    unsigned threads = 0;
+    size_t chunk = 0, make = 0;
+    bool wants = false;
+};
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed);
 // Copies between caller memory and the device, after the work on s.  To the
 // host: complete when s has been waited for; from it: the host memory may be
 // reused when the call returns.

@@ -1,0 +1,109 @@
+// Host-side checks of rules that choose between paths, built like the other
+// host checks with sanitizers and without kernels: how a transfer between
+// caller memory and the device goes (copy_plan).
+#include "../../include/lbm3d.h"
+#include "../../paper_1010_4135_amd/csrc/lbm3d_api_impl.h"
+#include "../../paper_1010_4135_amd/csrc/lbm3d_internal.h"
+
+#include <cstdio>
+#include <random>
+
+namespace lbm3d {
+hipError_t launch_init(int, const Grid&, const Model<double>&, const double*, void*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_step(int, const Grid&, const FaceBC&, const TileCfg&, const Model<double>&, const Model<float>&,
+                       const double (*)[5], const void*, void*, uint32_t*, hipStream_t, bool, hipEvent_t,
+                       hipEvent_t) { return hipErrorNoDevice; }
+hipError_t launch_ghosts(int, const Grid&, const FaceBC&, const Model<double>&, const double (*)[5], bool, void*,
+                         hipStream_t, uint32_t) { return hipErrorNoDevice; }
+hipError_t launch_moments(int, const Grid&, const Model<double>&, const void*, double*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_conserved(int, const Grid&, const Model<double>&, const void*, double*, int, double*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_pack(int, const Grid&, const void*, void*, bool, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_batch_layers(int, const BatchSolve*, const BatchLayerJob*, const int32_t*, int, int, const BatchCount*,
+                               hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_gather_health(const BatchSolve*, int, uint32_t*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_batch_step(int, int, bool, const BatchSolve*, const BatchTile*, BatchQueue*, int, int, int,
+                             const BatchCount*, hipStream_t) { return hipErrorNoDevice; }
+}  // namespace lbm3d
+
+static int failures = 0;
+#define EXPECT(c)                                                            \
+    do {                                                                     \
+        if (!(c)) {                                                          \
+            std::fprintf(stderr, "check failed line %d: %s\n", __LINE__, #c); \
+            failures++;                                                      \
+        }                                                                    \
+    } while (0)
+
+static constexpr size_t MIB = (size_t)1 << 20;
+
+// The buffer as the transfers of a process leave it.
+struct Process {
+    size_t buffer = 0, passed = 0;
+    int made = 0;
+    lbm3d::CopyPlan move(size_t bytes, bool down)
+    {
+        const lbm3d::CopyPlan p = lbm3d::copy_plan(bytes, down, buffer, passed);
+        if (p.make) {
+            buffer = p.make;
+            made++;
+        }
+        if (!p.threads && p.wants) passed += bytes;
+        return p;
+    }
+};
+
+static void check_copies(std::mt19937& rng)
+{
+    // a solve that is initialised, read back a few times, saved and destroyed
+    // makes no buffer unless one of its transfers repays it
+    for (size_t mib : {1, 3, 5, 10, 12, 20, 31}) {
+        Process p;
+        p.move(mib * MIB, false);
+        p.move(mib * MIB, true);
+        p.move(mib * MIB * 3 / 2, true);
+        EXPECT(p.made == (mib * 3 / 2 >= 32 ? 1 : 0));
+    }
+    // read back again and again, it is made once and then used
+    for (size_t mib : {4, 10, 31}) {
+        Process p;
+        int first = -1;
+        for (int k = 0; k < 60; k++) {
+            const lbm3d::CopyPlan c = p.move(mib * MIB, true);
+            if (c.threads && first < 0) first = k;
+            EXPECT((c.threads != 0) == (first >= 0));
+        }
+        EXPECT(p.made == 1 && first >= 0 && (size_t)(first + 1) * mib >= 128 && (size_t)first * mib < 128);
+        // a larger transfer needs a larger one, a smaller none
+        EXPECT(p.move(200 * MIB, false).make != 0 && p.move(mib * MIB, true).make == 0 && p.made == 2);
+    }
+    // below these sizes the runtime has no disadvantage to make good
+    EXPECT(!lbm3d::copy_plan(4 * MIB - 1, true, 32 * MIB, 0).threads && !lbm3d::copy_plan(4 * MIB - 1, true, 0, 1 << 30).wants);
+    EXPECT(!lbm3d::copy_plan(32 * MIB - 1, false, 32 * MIB, 0).threads);
+    // every worker has a slot of its own within the buffer, and the chunks are
+    // no smaller than they need be
+    for (int k = 0; k < 20000; k++) {
+        const size_t bytes = 1 + (size_t)(rng() % 300000) * 1021, buffers[3] = {0, 6 * MIB, 32 * MIB};
+        const size_t buffer = buffers[rng() % 3], passed = (size_t)(rng() % 200) * MIB;
+        const lbm3d::CopyPlan c = lbm3d::copy_plan(bytes, rng() % 2, buffer, passed);
+        if (!c.threads) {
+            EXPECT(c.make == 0);
+            continue;
+        }
+        EXPECT(c.wants && c.threads <= 8 && c.chunk > 0 && c.chunk % 65536 == 0);
+        EXPECT(c.threads * c.chunk <= (c.make ? c.make : buffer));
+        EXPECT(c.make == 0 || c.make > buffer);
+        EXPECT(c.chunk >= 2 * MIB || c.threads * c.chunk >= bytes);
+    }
+}
+
+int main()
+{
+    std::mt19937 rng(4711);
+    check_copies(rng);
+    if (failures) {
+        std::fprintf(stderr, "%d rule checks failed\n", failures);
+        return 1;
+    }
+    std::printf("rule checks passed\n");
+    return 0;
+}
