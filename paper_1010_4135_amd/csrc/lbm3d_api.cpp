@@ -283,9 +283,18 @@ static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipEr
         }
         g_staging_bytes = plan.make;
     }
-    int device = 0;
-    hipError_t first = hipGetDevice(&device);
-    if (first != hipSuccess) return false;
+    // events belong to the device current when they are made and are recorded
+    // on streams of it only: that of s, which the caller may have left
+    int device = 0, mine = 0;
+    if (hipStreamGetDevice(s, &device) != hipSuccess || hipGetDevice(&mine) != hipSuccess ||
+        hipSetDevice(device) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    struct Back {
+        int device;
+        ~Back() { (void)hipSetDevice(device); }
+    } back{mine};
     hipEvent_t done[COPY_THREADS] = {};
     for (unsigned t = 0; t < plan.threads; t++)
         if (hipEventCreateWithFlags(&done[t], hipEventDisableTiming) != hipSuccess) {

@@ -73,3 +73,27 @@ def test_threads_copy_at_once(buffer):
         assert np.array_equal(put, got)
         m2, f2, _, _ = _round_trip(c, k)
         assert np.array_equal(f, f2) and all(np.array_equal(a, b) for a, b in zip(m, m2))
+
+
+def test_with_another_device_current():
+    """Fields of a solve on device 0 in and out while the caller's thread has
+    device 1 current, which it keeps."""
+    import ctypes
+
+    from paper_1010_4135_amd import lbm3d
+    if lbm3d.lbm3d_device_count() < 2:
+        pytest.skip("needs two devices")
+    hip = ctypes.CDLL("libamdhip64.so")
+    now = ctypes.c_int()
+    c = inputs.smooth_periodic(43, grid=(96, 96, 96), precision=inputs.FP64)
+    with lbm3d.Solver(c.params) as s:
+        s.init(*c.fields)
+        want = s.moments()
+        try:
+            assert hip.hipSetDevice(1) == 0
+            s.init(*c.fields)
+            got = s.moments()
+            assert hip.hipGetDevice(ctypes.byref(now)) == 0 and now.value == 1
+        finally:
+            hip.hipSetDevice(0)
+        assert all(np.array_equal(a, b) for a, b in zip(want, got))
