@@ -68,9 +68,9 @@ struct CopyPlan {
     bool wants = false;
 };
 CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed);
-// Copies between caller memory and the device, after the work on s.  To the
-// host: complete when s has been waited for; from it: the host memory may be
-// reused when the call returns.
+// Copies between caller memory and the device, after the work on s, complete
+// when s has been waited for; until then the host memory must stay as it is,
+// in both directions (pinned memory is read by the device itself).
 hipError_t copy_to_host(const HostCopy* items, int n, hipStream_t s);
 hipError_t copy_to_device(const HostCopy* items, int n, hipStream_t s);
 // The pinned buffer those copies go through exists while a user of it does
