@@ -309,10 +309,11 @@ int32_t lbm3d_set_f(lbm3d_t h, const void* host, size_t bytes);
  * 64 x BY x TZ tiles from per-XCD work lists (see lbm3d_batch_plan).  A
  * member takes part while it has steps to do (a device-side count per
  * member), and runs of 16 steps are replayed from a captured HIP graph.
- * Results are bitwise identical to stepping each solve alone.  Blocking.  E_INVAL for mixed precisions, duplicate or NULL
- * handles, count < 1, a negative step count, a solve with the
- * second-order upwind flag, or one beyond the tiled kernels' 32-bit
- * offsets (a velocity-major level whose velocity block reaches 2 GiB).
+ * Results are bitwise identical to stepping each solve alone.  Blocking.
+ * E_INVAL for mixed precisions, duplicate or NULL handles, count < 1, a
+ * negative step count, a solve with the second-order upwind flag, or one
+ * beyond the tiled kernels' 32-bit offsets (a velocity-major level whose
+ * velocity block reaches 2 GiB).
  * E_STATE if a member is not initialised. */
 int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* nsteps);
 
@@ -321,12 +322,13 @@ int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* nsteps);
  * step as lbm3d_batch_step, with the same arguments, errors and results
  * (bitwise), that allocates nothing.  Its work tables (the solve table,
  * tile lists, counters, boundary-layer jobs, step counts and health words) go into a
- * static device array of 16 MiB per device, held until the process ends,
+ * static device array of 4 MiB per device, held until the process ends,
  * instead of a hipMalloc'd buffer; they are copied there from host memory
  * with hipMemcpyAsync on the first member's stream, and every step is
  * launched directly (no graph is instantiated).  A batch is taken whose
- * tables, were every member tiled, fit 4 MiB: up to about 200,000 tiles (20 B each, plus about 0.5 KB per solve); the
- * benchmark's mix of 64 uneven solves needs about 0.1 MB at the default tile depth.
+ * tables, were every member tiled, fit 4 MiB: up to about 200,000 tiles
+ * (20 B each, plus about 0.5 KB per solve); the benchmark's mix of 64 uneven
+ * solves needs about 0.1 MB at the default tile depth.
  * E_NOMEM, before any device work, for a batch whose tables exceed it.
  * All calls on one device share the array: calls that overlap on one device
  * (from several threads or streams) race and must be serialised.  Like
@@ -336,8 +338,8 @@ int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const int64_t* nste
 
 /* Work plan of the batched step's tiled launch, computed on the host (no
  * device work; solves that the batched step takes by blocks instead are
- * planned as if tiled): the tiles of solves with parameters ps[0..count-1] (validated as lbm3d_create,
- * all of one precision) at tile depth tz (0: the tuned depth of the
+ * planned as if tiled): the tiles of solves with parameters
+ * ps[0..count-1] (validated as lbm3d_create, all of one precision) at tile depth tz (0: the tuned depth of the
  * precision, else a launch model's for these solves; < 0: the model's; a
  * depth at or beyond a solve's nz gives whole columns), for a device of
  * `cus` compute units.  Tiles are 64 x BY nodes in x-y (BY = 4 in FP64, 8

@@ -315,6 +315,14 @@ static double blocks_us(int mode, const std::vector<BatchMember>& members, const
     return 2.5 + blocks * (mode == LBM3D_FP64 ? 0.017 : 0.007) * 256.0 / cus;
 }
 
+static std::vector<GroupMembers> all_tiled(size_t members)
+{
+    GroupMembers all;
+    all.tiled = true;
+    for (size_t k = 0; k < members; k++) all.who.push_back((int32_t)k);
+    return {all};
+}
+
 std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& members, int tz, int cus)
 {
     const int by = mode == LBM3D_FP64 ? 4 : 8;
@@ -328,10 +336,7 @@ std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& 
         }
         if (apart <= tiled_us(mode, members, tz, by, cus)) return parts;
     }
-    GroupMembers all;
-    all.tiled = true;
-    for (size_t k = 0; k < members.size(); k++) all.who.push_back((int32_t)k);
-    return {all};
+    return all_tiled(members.size());
 }
 
 int batch_model_depth(int mode, const std::vector<BatchMember>& members, int cus)
@@ -400,50 +405,34 @@ size_t BatchPlan::table_bytes(const std::vector<lbm3d_solver*>& members, int tz)
     return tables_need(members.size(), p.tiles.size(), lj.size(), (size_t)nlb);
 }
 
-int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t s, int tz, void* dev, size_t cap)
+// The tables, laid out in a host image of the device memory: the solves in
+// group order and the members' health words, then per group its queue, counts
+// and work items (with the solves' indices in the group).
+int32_t BatchPlan::lay_out(const std::vector<BatchMember>& shapes, const std::vector<GroupMembers>& parts, int tz,
+                           int cus, Layout& t)
 {
-    // work still queued may read the old tables or replay the old graphs
-    if (last_stream_ && hipStreamSynchronize(last_stream_) != hipSuccess) return LBM3D_E_DEVICE;
-    last_stream_ = nullptr;
-    release_graphs();
-    members_.clear();
+    groups_.clear();
     order_.clear();
-    count_pending_ = false;
-    if (members.empty()) return LBM3D_OK;
-    mode_ = members[0]->mode;
-    by_ = mode_ == LBM3D_FP64 ? 4 : 8;
-    const int cus = device_cus();
-
-    // The tables, laid out in a host image of the device memory: the solves
-    // in group order and the members' health words, then per group its
-    // queue, counts and work items (with the solves' indices in the group).
-    std::vector<char> image;
+    t = Layout();
+    std::vector<char>& image = t.image;
     auto place = [&](size_t bytes) {
         const size_t at = align256(image.size());
         image.resize(at + bytes, 0);
         return at;
     };
-    std::vector<BatchMember> shapes;
-    for (lbm3d_solver* h : members) shapes.push_back(BatchMember{h->g, h->bc});
-    const std::vector<GroupMembers> parts = plan_groups(mode_, shapes, tz, cus);
-    const size_t solves_at = place(members.size() * sizeof(BatchSolve));
-    const size_t health_at = place(members.size() * sizeof(uint32_t));
-    struct Offsets {
-        size_t queue, counts, items, grids, layers, blockjob;
-    };
-    std::vector<Offsets> offs;
+    t.solves = place(shapes.size() * sizeof(BatchSolve));
+    t.health = place(shapes.size() * sizeof(uint32_t));
     for (const GroupMembers& part : parts) {
         Group q;
-        q.first = (int)members_.size();
+        q.first = (int)order_.size();
         q.n = (int)part.who.size();
         q.tiled = part.tiled;
         std::vector<BatchMember> mine;
         for (int32_t k : part.who) {
-            members_.push_back(members[(size_t)k]);
             order_.push_back(k);
             mine.push_back(shapes[(size_t)k]);
         }
-        Offsets o{};
+        Layout::Offsets o{};
         o.queue = place(sizeof(BatchQueue));
         o.counts = place(2 * mine.size() * sizeof(BatchCount));
         std::vector<BatchTile> items;
@@ -462,11 +451,7 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
             q.stream = level_bytes > STREAM_MIN_BYTES && 2 * dense_bytes > level_bytes;
             TilePlan plan;
             int32_t rc = plan_tiles(grids, by_, plan_depth(mode_, tz, grids, by_, cus), cus, plan);
-            if (rc) {
-                release_graphs();
-                members_.clear();
-                return rc;
-            }
+            if (rc) return rc;
             items.swap(plan.tiles);
             q.nlists = plan.nlists;
             q.nblocks = plan.nblocks;
@@ -495,39 +480,55 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         o.items = place(items.size() * sizeof(BatchTile));
         std::memcpy(image.data() + o.items, items.data(), items.size() * sizeof(BatchTile));
         groups_.push_back(q);
-        offs.push_back(o);
+        t.groups.push_back(o);
     }
-    const size_t need = image.size();
+    return LBM3D_OK;
+}
+
+int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t s, int tz, void* dev, size_t cap)
+{
+    // work still queued may read the old tables or replay the old graphs
+    if (last_stream_ && hipStreamSynchronize(last_stream_) != hipSuccess) return LBM3D_E_DEVICE;
+    last_stream_ = nullptr;
+    release_graphs();
+    members_.clear();
+    count_pending_ = false;
+    if (members.empty()) return LBM3D_OK;
+    mode_ = members[0]->mode;
+    by_ = mode_ == LBM3D_FP64 ? 4 : 8;
+    const int cus = device_cus();
+    std::vector<BatchMember> shapes;
+    for (lbm3d_solver* h : members) shapes.push_back(BatchMember{h->g, h->bc});
+    Layout t;
+    int32_t rc = lay_out(shapes, plan_groups(mode_, shapes, tz, cus), tz, cus, t);
+    // tables of groups may need more room than those of one tiled plan (an
+    // entry per 64 blocks of a member, where a deep tile takes as many bytes
+    // for more nodes)
+    if (rc == LBM3D_OK && dev && t.image.size() > cap) rc = lay_out(shapes, all_tiled(shapes.size()), tz, cus, t);
+    const size_t need = t.image.size();
     char* base = (char*)dev;
-    if (dev) {
-        if (need > cap) {
-            release_graphs();
-            members_.clear();
-            return LBM3D_E_NOMEM;
-        }
+    if (rc == LBM3D_OK && dev && need > cap) rc = LBM3D_E_NOMEM;
+    if (rc == LBM3D_OK && (dev || need > dbytes_)) {
         if (dmem_) (void)hipFree(dmem_);
         dmem_ = nullptr;
         dbytes_ = 0;
-    } else {
-        if (need > dbytes_) {
-            if (dmem_) (void)hipFree(dmem_);
-            dmem_ = nullptr;
-            dbytes_ = 0;
-            hipError_t e = hipMalloc(&dmem_, need);
-            if (e != hipSuccess) {
-                release_graphs();
-                members_.clear();
-                return herr(e);
-            }
-            dbytes_ = need;
+        if (!dev) {
+            rc = herr(hipMalloc(&dmem_, need));
+            if (rc == LBM3D_OK) dbytes_ = need;
         }
-        base = (char*)dmem_;
     }
-    dsolves_ = (BatchSolve*)(base + solves_at);
-    dhealth_ = (uint32_t*)(base + health_at);
+    if (rc) {
+        groups_.clear();
+        return rc;
+    }
+    if (!dev) base = (char*)dmem_;
+    for (int32_t k : order_) members_.push_back(members[(size_t)k]);
+    std::vector<char>& image = t.image;
+    dsolves_ = (BatchSolve*)(base + t.solves);
+    dhealth_ = (uint32_t*)(base + t.health);
     for (size_t j = 0; j < groups_.size(); j++) {
         Group& q = groups_[j];
-        const Offsets& o = offs[j];
+        const Layout::Offsets& o = t.groups[j];
         q.queue = (BatchQueue*)(base + o.queue);
         q.counts = (BatchCount*)(base + o.counts);
         q.items = (BatchTile*)(base + o.items);
@@ -553,7 +554,7 @@ int32_t BatchPlan::build(const std::vector<lbm3d_solver*>& members, hipStream_t 
         d.health = h->health;
         d.md = h->md;
         d.mf = h->mf;
-        std::memcpy(image.data() + solves_at + k * sizeof(BatchSolve), &d, sizeof(d));
+        std::memcpy(image.data() + t.solves + k * sizeof(BatchSolve), &d, sizeof(d));
     }
     hcount_.assign(members_.size(), BatchCount{0, 0});
     // the tiles read some layers from memory, which members that last
@@ -758,12 +759,15 @@ extern "C" int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* n
 // stand-in: the device address of each device's copy comes from
 // hipGetSymbolAddress and is kept per device.
 // A batch is taken if its tables with every member tiled in one group fit
-// NOALLOC_SCRATCH_BYTES; the array holds a margin above that for what the
-// groups need beyond it (a second copy of the counts, a block grid and an
-// entry per untiled member and 16 K nodes, and up to 2 KB of alignment per
-// group, of which there are at most as many as 96 MiB go into the device).
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)4 << 20, NOALLOC_MARGIN = (size_t)12 << 20;
-static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES + NOALLOC_MARGIN];
+// NOALLOC_SCRATCH_BYTES, and goes that way where those of its groups do not
+// fit; the slack is for what build adds to the former (a second copy of the
+// counts, a longer queue).
+constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)4 << 20, NOALLOC_SLACK = (size_t)64 << 10;
+static_assert(NOALLOC_SCRATCH_BYTES / sizeof(BatchSolve) * sizeof(BatchCount) + 4096 <= NOALLOC_SLACK,
+              "as many members as there is room for");
+static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK];
+
+size_t lbm3d::noalloc_scratch_bytes() { return sizeof(scratch); }
 
 namespace {
 std::mutex g_scratch_mu;
@@ -804,7 +808,7 @@ extern "C" int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const in
     for (int32_t k = 1; k < count; k++)
         if (hs[k]->stream != s && hipStreamSynchronize(hs[k]->stream) != hipSuccess) return LBM3D_E_DEVICE;
     BatchPlan plan;  // tables in the scratch array, steps launched directly (no graph)
-    return batch_advance(hs, count, nsteps, s, plan, ptr, NOALLOC_SCRATCH_BYTES + NOALLOC_MARGIN, false);
+    return batch_advance(hs, count, nsteps, s, plan, ptr, NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK, false);
 }
 
 extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus,

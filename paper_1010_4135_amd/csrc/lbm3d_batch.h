@@ -62,7 +62,8 @@ public:
     // depth of the precision, else the launch model's; < 0 the launch model's.
     // The device tables go into a buffer the plan allocates, or, with
     // `dev` != nullptr, into the caller's `cap` bytes at `dev` (then nothing
-    // is allocated and E_NOMEM is returned if they do not fit).
+    // is allocated; the members go tiled in one group if the tables of more
+    // groups do not fit, and E_NOMEM is returned if those do not either).
     int32_t build(const std::vector<lbm3d_solver*>& members, hipStream_t s, int tz = 0,
                   void* dev = nullptr, size_t cap = 0);
     // Device bytes the tables of `members` need at tile depth tz (0: the
@@ -96,6 +97,17 @@ private:
         int32_t* blockjob = nullptr;      // job of each boundary-layer workgroup
         hipGraphExec_t graph = nullptr;
     };
+    // A plan's tables as they go to the device, and where they lie there.
+    struct Layout {
+        struct Offsets {
+            size_t queue, counts, items, grids, layers, blockjob;
+        };
+        std::vector<char> image;
+        size_t solves = 0, health = 0;
+        std::vector<Offsets> groups;
+    };
+    int32_t lay_out(const std::vector<BatchMember>& shapes, const std::vector<GroupMembers>& parts, int tz, int cus,
+                    Layout& t);  // fills groups_ and order_ too
     hipError_t enqueue(const Group& q, int parity, hipStream_t s);  // parity < 0: by the counts (-1, -2: which copy)
     void release_graphs();
 
@@ -112,6 +124,9 @@ private:
     hipStream_t capture_stream_ = nullptr;
     hipStream_t last_stream_ = nullptr;  // stream of the last enqueued work (drained before teardown)
 };
+
+// Bytes of the static device array of the step that allocates nothing.
+size_t noalloc_scratch_bytes();
 
 // Checks shared by the batched entry points (E_INVAL / E_STATE).
 int32_t check_batch(lbm3d_t* hs, int32_t count);

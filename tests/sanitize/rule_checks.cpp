@@ -1,11 +1,14 @@
 // Host-side checks of rules that choose between paths, built like the other
 // host checks with sanitizers and without kernels: how a transfer between
-// caller memory and the device goes (copy_plan).
+// caller memory and the device goes (copy_plan), and what the batched step
+// does where the tables of its groups do not fit the room it is given.
 #include "../../include/lbm3d.h"
 #include "../../paper_1010_4135_amd/csrc/lbm3d_api_impl.h"
+#include "../../paper_1010_4135_amd/csrc/lbm3d_batch.h"
 #include "../../paper_1010_4135_amd/csrc/lbm3d_internal.h"
 
 #include <cstdio>
+#include <cstring>
 #include <random>
 
 namespace lbm3d {
@@ -96,10 +99,57 @@ static void check_copies(std::mt19937& rng)
     }
 }
 
+// A solve as far as a plan looks at it (nothing of it is on a device).
+static void shape(lbm3d_solver& h, int nx, int ny, int nz, int precision)
+{
+    std::memset(&h.p, 0, sizeof h.p);
+    h.p.nx = nx;
+    h.p.ny = ny;
+    h.p.nz = nz;
+    h.p.precision = precision;
+    h.mode = precision;
+    h.g = lbm3d::make_grid(&h.p);
+}
+
+// Bytes build asks for: the least room it does not refuse (with room, it fails
+// where it would copy the tables to the device that is not there).
+static size_t room(const std::vector<lbm3d_solver*>& members, int tz)
+{
+    static char somewhere[256];
+    size_t lo = 0, hi = (size_t)1 << 26;  // refused, enough
+    while (hi - lo > 1) {
+        lbm3d::BatchPlan plan;
+        const size_t mid = (lo + hi) / 2;
+        const int32_t rc = plan.build(members, nullptr, tz, somewhere, mid);
+        EXPECT(rc == LBM3D_E_NOMEM || rc == LBM3D_E_DEVICE);
+        (rc == LBM3D_E_NOMEM ? lo : hi) = mid;
+    }
+    return hi;
+}
+
+static void check_tables()
+{
+    EXPECT(lbm3d::noalloc_scratch_bytes() <= 4 * MIB + MIB / 16);
+    // thin and long: by blocks an entry per 64 planes, in few tiles if tiled
+    for (int precision : {LBM3D_FP64, LBM3D_FP32}) {
+        lbm3d_solver a, b;
+        shape(a, 3, 2, 60000, precision);
+        shape(b, 9, 4, 30000, precision);
+        const std::vector<lbm3d_solver*> members{&a, &b};
+        std::vector<lbm3d::BatchMember> shapes;
+        for (lbm3d_solver* h : members) shapes.push_back(lbm3d::BatchMember{h->g, h->bc});
+        EXPECT(!lbm3d::plan_groups(precision, shapes, 0, lbm3d::device_cus())[0].tiled);
+        const int depth = lbm3d::batch_model_depth(precision, shapes, lbm3d::device_cus());
+        const size_t tiled = room(members, depth);
+        EXPECT(room(members, 0) == tiled && tiled <= lbm3d::BatchPlan::table_bytes(members) + 1024);
+    }
+}
+
 int main()
 {
     std::mt19937 rng(4711);
     check_copies(rng);
+    check_tables();
     if (failures) {
         std::fprintf(stderr, "%d rule checks failed\n", failures);
         return 1;
