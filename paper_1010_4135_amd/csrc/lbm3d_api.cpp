@@ -132,40 +132,43 @@ size_t footprint_of(const lbm3d_params* p)
 // of 4.7, an FP64 state of it (252 MB, fresh memory) 14 instead of 27.
 namespace lbm3d {
 
-constexpr unsigned COPY_THREADS = 8, COPY_FEW = 3;
-constexpr size_t COPY_SLOT = (size_t)4 << 20, COPY_FEW_SLOT = (size_t)2 << 20;  // bytes of a slot, the largest chunk
+constexpr unsigned COPY_THREADS = 8, COPY_FEW = 5;
+constexpr size_t COPY_SLOT = (size_t)4 << 20, COPY_SMALL_SLOT = (size_t)2 << 20;  // bytes of a slot, the largest chunk
 constexpr size_t COPY_HOST_CHUNK = (size_t)1 << 20, COPY_HOST_MIN = (size_t)2 << 20;  // copies within the host
 // Below COPY_MIN (to the host) and COPY_MIN_UP, one thread and the runtime's
-// own path: starting threads and a wait per chunk cost some 0.1 ms (3 MiB to
-// the host 0.17 - 0.20 ms either way, 5 MiB 0.22 and 0.30); from the host, the
-// runtime stages small copies at 30 GB/s (16 MB 0.52 ms against 0.66, 24 MB
-// 0.81 against 0.93) and large ones at 8 (126 MB 15.6 ms against 5.9).  From
-// COPY_MANY on a single array is memory fresh from the system, where page
-// faults need the eight threads (31 MiB: 0.90 ms with three threads and 0.91
-// with eight; 40 MiB: 4.5 and 2.7, the runtime 9.8).  Slots of 1 MiB: 16 MiB
-// 0.61 ms with three threads instead of 0.54, of 4 MiB no faster; with eight
-// threads 84 MiB 2.06 ms with 4 MiB and 2.25 with 2.
-constexpr size_t COPY_MIN = (size_t)4 << 20, COPY_MIN_UP = (size_t)32 << 20, COPY_MANY = (size_t)32 << 20;
+// own path: to the host, starting the threads costs some 0.1 ms (3 MiB 0.18 -
+// 0.25 ms either way); from it, the runtime stages small copies at 30 GB/s (16
+// MB 0.52 ms against 0.66, 24 MB 0.81 against 0.93) and large ones at 8 (126 MB
+// 15.6 ms against 5.9).  To the host, in memory touched before and in memory
+// fresh from the system, whose page faults are shared out: 4 MiB by the runtime
+// 0.22 and 0.85 ms, by five threads 0.23 and 0.45, by eight 0.30 and 0.45; 10
+// MiB 0.60 and 2.5, 0.40 and 1.0, 0.44 and 0.86; 24 MiB 1.4 and 5.8, 0.76 and
+// 2.1, 0.79 and 1.7.  Hence five threads below COPY_FEW_BELOW and eight above.
+// Slots of 2 MiB (1 MiB: 24 MiB 0.93 ms instead of 0.79), and of 4 MiB where
+// the buffer is worth it (84 MiB 2.06 ms instead of 2.25).
+constexpr size_t COPY_MIN = (size_t)4 << 20, COPY_FEW_BELOW = (size_t)10 << 20;
+constexpr size_t COPY_MIN_UP = (size_t)32 << 20, COPY_MANY = (size_t)32 << 20;
 
-// Making the buffer costs 1.5 - 2.5 ms (its pages are faulted in), and with its
-// release the next solve's first transfers take some 3 ms longer, where a
+// Making the buffer costs 1.5 - 2.5 ms (its pages are faulted in) where a
 // transfer of 10 MiB gains 0.2 ms and one of 20 MiB 0.5.  So it is made by a
-// transfer that gains more than that by itself (COPY_MANY), or once as much
-// has gone through the runtime for want of it as would have paid for it
-// (COPY_EARN): short-lived solves do not pay for it (64^3 created, stepped,
-// read back and destroyed: 1.6 ms, and 5.3 - 6.5 with a buffer each time).
-constexpr size_t COPY_EARN = (size_t)128 << 20;
-CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed)
+// transfer that gains more than that by itself (COPY_MANY), beside that much
+// work still queued on the device (`beside`), or once as much has gone through
+// the runtime for want of it as would have paid for it (COPY_EARN).  A 64^3
+// solve created, stepped 5 times, read back and destroyed: 1.6 ms, and 5.3 -
+// 6.5 with a buffer each time; 96x64x64 stepped 250 times and read back: 4.5
+// ms with a buffer each time, 5.0 without.
+constexpr size_t COPY_EARN = (size_t)64 << 20;
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool beside)
 {
     CopyPlan p;
     if (total < (down ? COPY_MIN : COPY_MIN_UP)) return p;
     const bool many = total >= COPY_MANY;
-    const unsigned threads = many ? COPY_THREADS : COPY_FEW;
-    const size_t slot = many ? COPY_SLOT : COPY_FEW_SLOT;
+    const unsigned threads = total < COPY_FEW_BELOW ? COPY_FEW : COPY_THREADS;
+    const size_t slot = many ? COPY_SLOT : COPY_SMALL_SLOT;
     p.wants = true;
-    if (buffer < threads * slot) {
-        if (!many && passed + total < COPY_EARN) return p;
-        p.make = threads * slot;
+    if (buffer < COPY_THREADS * slot) {
+        if (!many && !beside && passed + total < COPY_EARN) return p;
+        p.make = COPY_THREADS * slot;
     }
     p.threads = threads;
     p.chunk = std::min(((total + threads - 1) / threads + 65535) & ~(size_t)65535, slot);
@@ -229,7 +232,7 @@ static bool bad_state(size_t n, const double* rho, const double* ux, const doubl
     return bad;
 }
 
-// The pinned buffer (6 or 32 MiB, see copy_plan), for one transfer at a time
+// The pinned buffer (16 or 32 MiB, see copy_plan), for one transfer at a time
 // (another one meanwhile takes the runtime's own path), given back with the
 // last user.
 static std::mutex g_staging_mu;       // held by the transfer that uses the buffer
@@ -252,7 +255,7 @@ void staging_unref()
 
 // Moves every chunk of the items through a slot; false (and nothing done) if
 // the buffer is in use or there is none.
-static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipError_t* result)
+static bool staged(const HostCopy* items, int n, bool down, bool beside, hipStream_t s, hipError_t* result)
 {
     struct Chunk {
         char* host;
@@ -263,7 +266,7 @@ static bool staged(const HostCopy* items, int n, bool down, hipStream_t s, hipEr
     for (int i = 0; i < n; i++) total += items[i].bytes;
     std::unique_lock<std::mutex> lk(g_staging_mu, std::try_to_lock);
     if (!lk.owns_lock()) return false;
-    const CopyPlan plan = copy_plan(total, down, g_staging_bytes, g_passed);
+    const CopyPlan plan = copy_plan(total, down, g_staging_bytes, g_passed, beside);
     if (!plan.threads) {
         if (plan.wants) g_passed += total;
         return false;
@@ -338,7 +341,7 @@ static bool pageable(const void* p)
     return a.type == hipMemoryTypeUnregistered;
 }
 
-static hipError_t copy_items(const HostCopy* items, int n, bool down, hipStream_t s)
+static hipError_t copy_items(const HostCopy* items, int n, bool down, bool beside, hipStream_t s)
 {
     size_t total = 0;
     bool plain = true;
@@ -348,7 +351,7 @@ static hipError_t copy_items(const HostCopy* items, int n, bool down, hipStream_
         for (int i = 0; i < n; i++) plain = plain && pageable(items[i].host);
     hipError_t e = hipSuccess;
     if (large && plain) try {
-            if (staged(items, n, down, s, &e)) return e;
+            if (staged(items, n, down, beside, s, &e)) return e;
         } catch (...) {
             // (no memory for the chunk list, before anything was copied)
         }
@@ -358,8 +361,11 @@ static hipError_t copy_items(const HostCopy* items, int n, bool down, hipStream_
                  : hipMemcpyAsync(items[i].dev, items[i].host, items[i].bytes, hipMemcpyHostToDevice, s);
     return e;
 }
-hipError_t copy_to_host(const HostCopy* items, int n, hipStream_t s) { return copy_items(items, n, true, s); }
-hipError_t copy_to_device(const HostCopy* items, int n, hipStream_t s) { return copy_items(items, n, false, s); }
+hipError_t copy_to_host(const HostCopy* items, int n, bool beside, hipStream_t s)
+{
+    return copy_items(items, n, true, beside, s);
+}
+hipError_t copy_to_device(const HostCopy* items, int n, hipStream_t s) { return copy_items(items, n, false, false, s); }
 
 }  // namespace lbm3d
 
@@ -465,6 +471,16 @@ static hipError_t refresh_layers(lbm3d_solver* h)
                                        ghost_faces(h->g, h->bc, true));
     if (e == hipSuccess) h->layers_stale = false;
     return e;
+}
+
+// Does the device still have some 2 ms of a solve's steps to do (64 M node
+// updates at 18 - 40 G/s, unless they have run since they were queued)?
+static bool stepping(lbm3d_solver* h)
+{
+    if ((h->steps - h->read_steps) * h->n < (int64_t)64 << 20) return false;
+    const bool busy = hipStreamQuery(h->stream) == hipErrorNotReady;
+    (void)hipGetLastError();
+    return busy;
 }
 
 int32_t solver_enqueue_steps(lbm3d_solver* h, int64_t nsteps)
@@ -592,7 +608,7 @@ int32_t lbm3d_init(lbm3d_t h, const double* rho, const double* ux, const double*
     HIPCHK(hipMemsetAsync(h->health, 0, sizeof(uint32_t), s));
     HIPCHK(hipStreamSynchronize(s));
     h->cur = 0;
-    h->steps = 0;
+    h->steps = h->read_steps = 0;
     h->layers_stale = false;
     h->initialised = true;
     return LBM3D_OK;
@@ -728,13 +744,15 @@ int32_t lbm3d_moments(lbm3d_t h, double* rho, double* ux, double* uy, double* uz
     if (!h) return LBM3D_E_INVAL;
     if (!h->initialised) return LBM3D_E_STATE;
     hipStream_t s = h->stream;
+    const bool beside = stepping(h);
+    h->read_steps = h->steps;
     HIPCHK(launch_moments(h->mode, h->g, h->md, h->f[h->cur], h->q5, s));
     double* dst[5] = {rho, ux, uy, uz, p};
     HostCopy down[5];
     int n = 0;
     for (int c = 0; c < 5; c++)
         if (dst[c]) down[n++] = HostCopy{dst[c], h->q5 + (size_t)c * h->n, (size_t)h->n * sizeof(double)};
-    HIPCHK(copy_to_host(down, n, s));
+    HIPCHK(copy_to_host(down, n, beside, s));
     uint32_t hw = 0;
     HIPCHK(hipMemcpyAsync(&hw, h->health, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -783,12 +801,14 @@ int32_t lbm3d_get_f(lbm3d_t h, void* host, size_t bytes)
     if (!h->initialised) return LBM3D_E_STATE;
     const size_t need = (size_t)NV * h->n * elem_size(h->mode);
     if (bytes != need) return LBM3D_E_INVAL;
+    const bool beside = stepping(h);
+    h->read_steps = h->steps;
     void* dense = nullptr;
     HIPCHK(hipMalloc(&dense, need));
     hipStream_t s = h->stream;
     hipError_t e = launch_pack(h->mode, h->g, h->f[h->cur], dense, true, s);
     const HostCopy down{host, dense, need};
-    if (e == hipSuccess) e = copy_to_host(&down, 1, s);
+    if (e == hipSuccess) e = copy_to_host(&down, 1, beside, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(dense);
     return dev_err(e);

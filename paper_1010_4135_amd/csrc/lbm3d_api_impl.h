@@ -27,6 +27,7 @@ struct lbm3d_solver {
     bool upwind2 = false;      // the second-order upwind variant (steps untiled)
     int cur = 0;               // buffer holding the current level
     int64_t steps = 0;
+    int64_t read_steps = 0;    // the step count when the fields or the state were last read back
     bool initialised = false;
     hipStream_t own_stream = nullptr;
     hipStream_t stream = nullptr;
@@ -59,19 +60,21 @@ struct HostCopy {
 };
 // How a transfer of `total` bytes goes when the pinned buffer has `buffer`
 // bytes (0: there is none) and `passed` bytes have gone through the runtime
-// for want of it: by `threads` threads in chunks of `chunk` bytes, after
-// making a buffer of `make` bytes if that is not 0, or, with no threads,
-// through the runtime, `wants` saying that the buffer would have served.
+// for want of it, `beside` long work queued on the device or not: by `threads`
+// threads in chunks of `chunk` bytes, after making a buffer of `make` bytes if
+// that is not 0, or, with no threads, through the runtime, `wants` saying that
+// the buffer would have served.
 struct CopyPlan {
     unsigned threads = 0;
     size_t chunk = 0, make = 0;
     bool wants = false;
 };
-CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed);
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool beside);
 // Copies between caller memory and the device, after the work on s, complete
 // when s has been waited for; until then the host memory must stay as it is,
-// in both directions (pinned memory is read by the device itself).
-hipError_t copy_to_host(const HostCopy* items, int n, hipStream_t s);
+// in both directions (pinned memory is read by the device itself).  `beside`:
+// the device has 2 ms of work and more to do before it.
+hipError_t copy_to_host(const HostCopy* items, int n, bool beside, hipStream_t s);
 hipError_t copy_to_device(const HostCopy* items, int n, hipStream_t s);
 // The pinned buffer those copies go through exists while a user of it does
 // (every solver and server is one).

@@ -43,9 +43,9 @@ static constexpr size_t MIB = (size_t)1 << 20;
 struct Process {
     size_t buffer = 0, passed = 0;
     int made = 0;
-    lbm3d::CopyPlan move(size_t bytes, bool down)
+    lbm3d::CopyPlan move(size_t bytes, bool down, bool beside = false)
     {
-        const lbm3d::CopyPlan p = lbm3d::copy_plan(bytes, down, buffer, passed);
+        const lbm3d::CopyPlan p = lbm3d::copy_plan(bytes, down, buffer, passed, beside);
         if (p.make) {
             buffer = p.make;
             made++;
@@ -75,19 +75,24 @@ static void check_copies(std::mt19937& rng)
             if (c.threads && first < 0) first = k;
             EXPECT((c.threads != 0) == (first >= 0));
         }
-        EXPECT(p.made == 1 && first >= 0 && (size_t)(first + 1) * mib >= 128 && (size_t)first * mib < 128);
+        EXPECT(p.made == 1 && first >= 0 && (size_t)(first + 1) * mib >= 64 && (size_t)first * mib < 64);
         // a larger transfer needs a larger one, a smaller none
         EXPECT(p.move(200 * MIB, false).make != 0 && p.move(mib * MIB, true).make == 0 && p.made == 2);
     }
+    // beside long work on the device the first read-back makes it
+    for (size_t mib : {4, 10, 31}) {
+        Process p;
+        EXPECT(p.move(mib * MIB, true, true).make != 0 && p.move(mib * MIB, true).make == 0 && p.made == 1);
+    }
     // below these sizes the runtime has no disadvantage to make good
-    EXPECT(!lbm3d::copy_plan(4 * MIB - 1, true, 32 * MIB, 0).threads && !lbm3d::copy_plan(4 * MIB - 1, true, 0, 1 << 30).wants);
-    EXPECT(!lbm3d::copy_plan(32 * MIB - 1, false, 32 * MIB, 0).threads);
+    EXPECT(!lbm3d::copy_plan(4 * MIB - 1, true, 32 * MIB, 0, true).threads && !lbm3d::copy_plan(4 * MIB - 1, true, 0, 1 << 30, true).wants);
+    EXPECT(!lbm3d::copy_plan(32 * MIB - 1, false, 32 * MIB, 0, false).threads);
     // every worker has a slot of its own within the buffer, and the chunks are
     // no smaller than they need be
     for (int k = 0; k < 20000; k++) {
-        const size_t bytes = 1 + (size_t)(rng() % 300000) * 1021, buffers[3] = {0, 6 * MIB, 32 * MIB};
+        const size_t bytes = 1 + (size_t)(rng() % 300000) * 1021, buffers[3] = {0, 16 * MIB, 32 * MIB};
         const size_t buffer = buffers[rng() % 3], passed = (size_t)(rng() % 200) * MIB;
-        const lbm3d::CopyPlan c = lbm3d::copy_plan(bytes, rng() % 2, buffer, passed);
+        const lbm3d::CopyPlan c = lbm3d::copy_plan(bytes, rng() % 2, buffer, passed, rng() % 2);
         if (!c.threads) {
             EXPECT(c.make == 0);
             continue;

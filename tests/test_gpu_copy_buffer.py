@@ -1,6 +1,6 @@
 """Transfers through the pinned buffer by few threads and by many, once it is
-there: made by a transfer of 32 MiB or more, or after 128 MiB have gone
-through the runtime.  No arithmetic is involved, so states come back bit for
+there: made by a transfer of 32 MiB or more, beside steps still queued, or after
+64 MiB have gone through the runtime.  No arithmetic is involved, so states come back bit for
 bit; the moments of one state are the same bits each time they are read."""
 import threading
 
@@ -54,6 +54,27 @@ def test_read_back_until_the_buffer_is_made():
         for k in range(16):
             assert all(np.array_equal(a, b) for a, b in zip(first, s.moments())), k
         assert np.array_equal(state, s.get_f())
+
+
+def test_made_beside_queued_steps():
+    """Read back with 300 steps queued and with none: the same bits."""
+    from paper_1010_4135_amd import lbm3d
+    c = inputs.smooth_periodic(43, grid=(64, 64, 64), precision=inputs.FP32)
+    out = []
+    for wait in (False, True):
+        with lbm3d.Solver(c.params) as s:
+            s.init(*c.fields)
+            s.step(300)
+            if wait:
+                s.sync()
+            m = s.moments()
+            s.step(300)
+            if wait:
+                s.sync()
+            out.append((m, s.get_f(), s.moments(), s.status()))
+    for a, b in zip(out[0][0] + out[0][2], out[1][0] + out[1][2]):
+        assert np.array_equal(a, b)
+    assert np.array_equal(out[0][1], out[1][1]) and out[0][3] == out[1][3]
 
 
 def test_threads_copy_at_once(buffer):
