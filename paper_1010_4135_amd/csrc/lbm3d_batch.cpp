@@ -204,12 +204,17 @@ static double plan_makespan(const std::vector<Grid>& grids, int by, int d, int c
     return plan_tiles(grids, by, d, cus, p) == LBM3D_OK ? plan_makespan(p) : tile_makespan(grids, by, d, cus);
 }
 
-// Tile depth of a membership: of 16, 32, ... up to whole columns, the
-// deepest whose plan's makespan is within 5% of the shortest: whole columns
-// for a batch as large as the 64-solve mix (as the tuner finds), short chunks
-// for a few solves, whose whole columns would leave most compute units idle.
-// Plans are made for the depths that can be among those only.
-static int model_depth(const std::vector<Grid>& grids, int by, int cus)
+// Tile depth of a membership, of 16, 32, ... up to whole columns: in the FP32
+// modes the deepest whose plan's makespan is within 5% of the shortest (whole
+// columns for a batch as large as the 64-solve mix, as the tuner finds, short
+// chunks for a few solves, whose whole columns would leave most compute units
+// idle); in FP64, which leans less on the caches, the shortest (the shallower
+// of two: 100x164x238 and 173x85x266 752 us a step with 32 planes, 761 with 64;
+// six solves of about 90^3 607 and 645).  Plans are made for the depths that
+// can be among those only.  Over 12 memberships of 1 - 20 solves, depths in
+// between tried too, this takes the fastest depth or one 1% behind in the FP32
+// modes, and one a few percent behind in FP64.
+static std::vector<std::pair<double, int>> least_makespans(const std::vector<Grid>& grids, int by, int cus)
 {
     int maxnz = 1;
     for (const Grid& g : grids) maxnz = std::max(maxnz, g.nz);
@@ -220,30 +225,33 @@ static int model_depth(const std::vector<Grid>& grids, int by, int cus)
         if (dd >= maxnz) break;
     }
     std::sort(least.begin(), least.end());
+    return least;
+}
+static int model_depth(int mode, const std::vector<Grid>& grids, int by, int cus, double* planes = nullptr)
+{
+    const double slack = mode == LBM3D_FP64 ? 1.0 : 1.05;
     std::vector<std::pair<double, int>> tried;
     double best = 0.0;
-    for (const auto& c : least) {
-        if (!tried.empty() && c.first > 1.05 * best) break;
+    for (const auto& c : least_makespans(grids, by, cus)) {
+        if (!tried.empty() && c.first > slack * best) break;
         tried.emplace_back(plan_makespan(grids, by, c.second, cus), c.second);
         best = tried.size() == 1 ? tried[0].first : std::min(best, tried.back().first);
     }
-    int depth = 0;
+    std::pair<double, int> pick{0.0, 0};
     for (const auto& t : tried)
-        if (t.first <= 1.05 * best) depth = std::max(depth, t.second);
-    return depth;
+        if (t.first <= slack * best && (pick.second == 0 || (mode != LBM3D_FP64) == (t.second > pick.second))) pick = t;
+    if (planes) *planes = pick.first;
+    return pick.second;
 }
 
 // Tile depth of a plan: tz > 0 as given; 0: the precision's tuned depth,
 // else the model's; < 0: the model's (memberships that change from tick to
 // tick, whose best depth no earlier tuning knows).
+static int fixed_depth(int mode, int tz) { return tz == 0 ? batch_tile_depth(mode) : std::max(tz, 0); }
 static int plan_depth(int mode, int tz, const std::vector<Grid>& grids, int by, int cus)
 {
-    if (tz > 0) return tz;
-    if (tz == 0) {
-        const int t = batch_tile_depth(mode);
-        if (t > 0) return t;
-    }
-    return model_depth(grids, by, cus);
+    const int t = fixed_depth(mode, tz);
+    return t > 0 ? t : model_depth(mode, grids, by, cus);
 }
 
 // Members are independent, so a run steps them group by group, all its steps
@@ -294,24 +302,20 @@ static std::vector<GroupMembers> group_members(int mode, const std::vector<Batch
     return out;
 }
 
-// Time of a step of tiled members or of one untiled group, from what the
-// headline solve and the groups above measured per plane of a tile and per
-// block (at 256 compute units), with their launches.
-static double tiled_us(int mode, const std::vector<BatchMember>& members, int tz, int by, int cus)
+// Time of a step of tiled members or of one untiled group, from what their
+// kernels take per plane of a tile (over the memberships above 3.1 - 3.8 us in
+// FP64, 2.5 - 3.6 in the FP32 modes) and per block (14 - 19 ns in FP64, 7 - 9 in
+// the FP32 modes, at 256 compute units), with their launches.
+static double tiled_us(int mode, double planes, const std::vector<BatchMember>& members)
 {
-    std::vector<Grid> grids;
     bool layers = false;
-    for (const BatchMember& m : members) {
-        grids.push_back(m.g);
-        layers = layers || ghost_faces(m.g, m.bc, true) != 0;
-    }
-    return plan_makespan(grids, by, plan_depth(mode, tz, grids, by, cus), cus) * (mode == LBM3D_FP64 ? 3.3 : 3.1) +
-           (layers ? 9.0 : 3.0);
+    for (const BatchMember& m : members) layers = layers || ghost_faces(m.g, m.bc, true) != 0;
+    return planes * (mode == LBM3D_FP64 ? 3.5 : 3.1) + (layers ? 9.0 : 3.0);
 }
-static double blocks_us(int mode, const std::vector<BatchMember>& members, const GroupMembers& part, int cus)
+static double blocks_us(int mode, const std::vector<BatchMember>& members, int cus)
 {
     double blocks = 0.0;
-    for (int32_t k : part.who) blocks += block_grid(members[(size_t)k].g).count;
+    for (const BatchMember& m : members) blocks += block_grid(m.g).count;
     return 2.5 + blocks * (mode == LBM3D_FP64 ? 0.017 : 0.007) * 256.0 / cus;
 }
 
@@ -325,25 +329,42 @@ static std::vector<GroupMembers> all_tiled(size_t members)
 
 std::vector<GroupMembers> plan_groups(int mode, const std::vector<BatchMember>& members, int tz, int cus)
 {
-    const int by = mode == LBM3D_FP64 ? 4 : 8;
-    if (tz <= 0 && !(tz == 0 && batch_depth_set(mode))) {
-        const std::vector<GroupMembers> parts = group_members(mode, members);
-        double apart = 0.0;
-        for (const GroupMembers& part : parts) {
-            std::vector<BatchMember> mine;
-            for (int32_t k : part.who) mine.push_back(members[(size_t)k]);
-            apart += part.tiled ? tiled_us(mode, mine, tz, by, cus) : blocks_us(mode, members, part, cus);
-        }
-        if (apart <= tiled_us(mode, members, tz, by, cus)) return parts;
+    const int by = mode == LBM3D_FP64 ? 4 : 8, fixed = fixed_depth(mode, tz);
+    if (tz > 0 || (tz == 0 && batch_depth_set(mode))) return all_tiled(members.size());
+    std::vector<GroupMembers> parts = group_members(mode, members);
+    if (parts.size() == 1 && parts[0].tiled) return parts;
+    auto grids_of = [](const std::vector<BatchMember>& who) {
+        std::vector<Grid> grids;
+        for (const BatchMember& m : who) grids.push_back(m.g);
+        return grids;
+    };
+    // a tiled group's time, and the depth that it takes
+    auto tiled = [&](const std::vector<BatchMember>& who, int* depth) {
+        const std::vector<Grid> grids = grids_of(who);
+        double planes = 0.0;
+        *depth = fixed > 0 ? fixed : model_depth(mode, grids, by, cus, &planes);
+        if (fixed > 0) planes = plan_makespan(grids, by, fixed, cus);
+        return tiled_us(mode, planes, who);
+    };
+    double apart = 0.0;
+    for (GroupMembers& part : parts) {
+        std::vector<BatchMember> mine;
+        for (int32_t k : part.who) mine.push_back(members[(size_t)k]);
+        apart += part.tiled ? tiled(mine, &part.depth) : blocks_us(mode, mine, cus);
     }
-    return all_tiled(members.size());
+    // (no plan of all members is made where it could not win at best)
+    const std::vector<Grid> grids = grids_of(members);
+    const double least = fixed > 0 ? tile_makespan(grids, by, fixed, cus) : least_makespans(grids, by, cus)[0].first;
+    if (apart <= tiled_us(mode, least, members)) return parts;
+    std::vector<GroupMembers> all = all_tiled(members.size());
+    return apart <= tiled(members, &all[0].depth) ? parts : all;
 }
 
 int batch_model_depth(int mode, const std::vector<BatchMember>& members, int cus)
 {
     std::vector<Grid> grids;
     for (const BatchMember& m : members) grids.push_back(m.g);
-    return model_depth(grids, mode == LBM3D_FP64 ? 4 : 8, cus);
+    return model_depth(mode, grids, mode == LBM3D_FP64 ? 4 : 8, cus);
 }
 
 // layer jobs of tiled members (faces the tiles leave to memory)
@@ -450,7 +471,8 @@ int32_t BatchPlan::lay_out(const std::vector<BatchMember>& shapes, const std::ve
             // line (in the FP32 modes), as for a single solve
             q.stream = level_bytes > STREAM_MIN_BYTES && 2 * dense_bytes > level_bytes;
             TilePlan plan;
-            int32_t rc = plan_tiles(grids, by_, plan_depth(mode_, tz, grids, by_, cus), cus, plan);
+            const int depth = part.depth > 0 ? part.depth : plan_depth(mode_, tz, grids, by_, cus);
+            int32_t rc = plan_tiles(grids, by_, depth, cus, plan);
             if (rc) return rc;
             items.swap(plan.tiles);
             q.nlists = plan.nlists;

@@ -35,6 +35,7 @@ struct GroupMembers {
     std::vector<int32_t> who;
     int64_t bytes = 0;
     bool tiled = false;
+    int depth = 0;  // of a tiled group, where the grouping has found it
 };
 // The groups of a plan at tile depth tz (as for BatchPlan::build): all members
 // tiled in one group where the caller asks for a depth (tz > 0, or the
