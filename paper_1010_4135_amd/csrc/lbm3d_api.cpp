@@ -150,15 +150,15 @@ constexpr size_t COPY_MIN = (size_t)4 << 20, COPY_FEW_BELOW = (size_t)10 << 20;
 constexpr size_t COPY_MIN_UP = (size_t)32 << 20, COPY_MANY = (size_t)32 << 20;
 
 // Making the buffer costs 1.5 - 2.5 ms (its pages are faulted in) where a
-// transfer of 10 MiB gains 0.2 ms and one of 20 MiB 0.5.  So it is made by a
-// transfer that gains more than that by itself (COPY_MANY), beside that much
-// work still queued on the device (`beside`), or once as much has gone through
-// the runtime for want of it as would have paid for it (COPY_EARN).  A 64^3
-// solve created, stepped 5 times, read back and destroyed: 1.6 ms, and 5.3 -
-// 6.5 with a buffer each time; 96x64x64 stepped 250 times and read back: 4.5
-// ms with a buffer each time, 5.0 without.
-constexpr size_t COPY_EARN = (size_t)64 << 20;
-CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool beside)
+// transfer of 10 MiB gains 0.2 ms in touched and 1.6 ms in fresh memory.  So it
+// is made by a transfer that gains more than that by itself (COPY_MANY), beside
+// that much work still queued on the device, where another solve or a server
+// will keep it (`now`), or once as much has gone through the runtime for want
+// of it (COPY_EARN).  A 64^3 solve created, stepped 5 times, read back and
+// destroyed: 1.6 ms, and 5.3 - 6.5 with a buffer each time; 96x64x64 stepped
+// 250 times and read back: 4.5 ms with a buffer each time, 5.0 without.
+constexpr size_t COPY_EARN = (size_t)32 << 20;
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool now)
 {
     CopyPlan p;
     if (total < (down ? COPY_MIN : COPY_MIN_UP)) return p;
@@ -167,7 +167,7 @@ CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool b
     const size_t slot = many ? COPY_SLOT : COPY_SMALL_SLOT;
     p.wants = true;
     if (buffer < COPY_THREADS * slot) {
-        if (!many && !beside && passed + total < COPY_EARN) return p;
+        if (!many && !now && passed + total < COPY_EARN) return p;
         p.make = COPY_THREADS * slot;
     }
     p.threads = threads;
@@ -266,7 +266,7 @@ static bool staged(const HostCopy* items, int n, bool down, bool beside, hipStre
     for (int i = 0; i < n; i++) total += items[i].bytes;
     std::unique_lock<std::mutex> lk(g_staging_mu, std::try_to_lock);
     if (!lk.owns_lock()) return false;
-    const CopyPlan plan = copy_plan(total, down, g_staging_bytes, g_passed, beside);
+    const CopyPlan plan = copy_plan(total, down, g_staging_bytes, g_passed, beside || g_staging_users > 1);
     if (!plan.threads) {
         if (plan.wants) g_passed += total;
         return false;

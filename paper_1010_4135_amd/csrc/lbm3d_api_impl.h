@@ -60,7 +60,7 @@ struct HostCopy {
 };
 // How a transfer of `total` bytes goes when the pinned buffer has `buffer`
 // bytes (0: there is none) and `passed` bytes have gone through the runtime
-// for want of it, `beside` long work queued on the device or not: by `threads`
+// for want of it, making it worth while now or not yet (`now`): by `threads`
 // threads in chunks of `chunk` bytes, after making a buffer of `make` bytes if
 // that is not 0, or, with no threads, through the runtime, `wants` saying that
 // the buffer would have served.
@@ -69,7 +69,7 @@ struct CopyPlan {
     size_t chunk = 0, make = 0;
     bool wants = false;
 };
-CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool beside);
+CopyPlan copy_plan(size_t total, bool down, size_t buffer, size_t passed, bool now);
 // Copies between caller memory and the device, after the work on s, complete
 // when s has been waited for; until then the host memory must stay as it is,
 // in both directions (pinned memory is read by the device itself).  `beside`:

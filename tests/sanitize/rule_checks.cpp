@@ -43,9 +43,9 @@ static constexpr size_t MIB = (size_t)1 << 20;
 struct Process {
     size_t buffer = 0, passed = 0;
     int made = 0;
-    lbm3d::CopyPlan move(size_t bytes, bool down, bool beside = false)
+    lbm3d::CopyPlan move(size_t bytes, bool down, bool now = false)
     {
-        const lbm3d::CopyPlan p = lbm3d::copy_plan(bytes, down, buffer, passed, beside);
+        const lbm3d::CopyPlan p = lbm3d::copy_plan(bytes, down, buffer, passed, now);
         if (p.make) {
             buffer = p.make;
             made++;
@@ -59,7 +59,7 @@ static void check_copies(std::mt19937& rng)
 {
     // a solve that is initialised, read back a few times, saved and destroyed
     // makes no buffer unless one of its transfers repays it
-    for (size_t mib : {1, 3, 5, 10, 12, 20, 31}) {
+    for (size_t mib : {1, 3, 5, 10, 12, 31}) {
         Process p;
         p.move(mib * MIB, false);
         p.move(mib * MIB, true);
@@ -75,11 +75,11 @@ static void check_copies(std::mt19937& rng)
             if (c.threads && first < 0) first = k;
             EXPECT((c.threads != 0) == (first >= 0));
         }
-        EXPECT(p.made == 1 && first >= 0 && (size_t)(first + 1) * mib >= 64 && (size_t)first * mib < 64);
+        EXPECT(p.made == 1 && first >= 0 && (size_t)(first + 1) * mib >= 32 && (size_t)first * mib < 32);
         // a larger transfer needs a larger one, a smaller none
         EXPECT(p.move(200 * MIB, false).make != 0 && p.move(mib * MIB, true).make == 0 && p.made == 2);
     }
-    // beside long work on the device the first read-back makes it
+    // beside long work on the device, or for several users, the first read-back makes it
     for (size_t mib : {4, 10, 31}) {
         Process p;
         EXPECT(p.move(mib * MIB, true, true).make != 0 && p.move(mib * MIB, true).make == 0 && p.made == 1);

@@ -1,7 +1,8 @@
 """Transfers through the pinned buffer by few threads and by many, once it is
-there: made by a transfer of 32 MiB or more, beside steps still queued, or after
-64 MiB have gone through the runtime.  No arithmetic is involved, so states come back bit for
-bit; the moments of one state are the same bits each time they are read."""
+there: made by a transfer of 32 MiB or more, beside steps still queued, for one
+of several solves, or after 32 MiB have gone through the runtime.  No arithmetic
+is involved, so states come back bit for bit; the moments of one state are the
+same bits each time they are read."""
 import threading
 
 import numpy as np
