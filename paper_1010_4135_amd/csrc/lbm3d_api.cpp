@@ -567,7 +567,10 @@ int32_t lbm3d_footprint(const lbm3d_params* p, size_t* bytes)
     return LBM3D_OK;
 }
 
-int32_t lbm3d_create(const lbm3d_params* p, lbm3d_t* out) { return solver_create(p, out); }
+int32_t lbm3d_create(const lbm3d_params* p, lbm3d_t* out)
+{
+    return no_throw([&] { return solver_create(p, out); });
+}
 
 int32_t lbm3d_destroy(lbm3d_t h)
 {
@@ -591,7 +594,7 @@ int32_t lbm3d_init(lbm3d_t h, const double* rho, const double* ux, const double*
     if (!h || !rho || !ux || !uy || !uz || !p) return LBM3D_E_INVAL;
     if (bad_state((size_t)h->n, rho, ux, uy, uz, p)) return LBM3D_E_INVAL;
     if (h->p.flags & LBM3D_CHECK_STABILITY) {
-        const int32_t rc = admission(&h->p, rho, ux, uy, uz, p, nullptr);
+        const int32_t rc = no_throw([&] { return admission(&h->p, rho, ux, uy, uz, p, nullptr); });
         if (rc) return rc;
     }
     hipStream_t s = h->stream;
@@ -640,7 +643,12 @@ int32_t lbm3d_step_profiled(lbm3d_t h, int64_t nsteps, double* total_ms, double*
 {
     if (!h || nsteps < 1) return LBM3D_E_INVAL;
     if (!h->initialised) return LBM3D_E_STATE;
-    std::vector<hipEvent_t> ev((size_t)2 * nsteps, nullptr);
+    std::vector<hipEvent_t> ev;
+    const int32_t room = no_throw([&]() -> int32_t {
+        ev.assign((size_t)2 * nsteps, nullptr);
+        return LBM3D_OK;
+    });
+    if (room != LBM3D_OK) return room;
     hipError_t e = hipSuccess;
     for (auto& x : ev)
         if (e == hipSuccess) e = hipEventCreate(&x);

@@ -50,6 +50,17 @@ size_t f_bytes(const Grid& g, int precision);
 size_t footprint_of(const lbm3d_params* p);
 int32_t solver_create(const lbm3d_params* p, lbm3d_solver** out);
 int32_t solver_enqueue_steps(lbm3d_solver* h, int64_t nsteps);
+// What f returns, or E_NOMEM if it throws: plans and their tables are host
+// allocations, and nothing may leave a C entry point, or end a server's worker.
+template <typename F>
+int32_t no_throw(F&& f) noexcept
+{
+    try {
+        return f();
+    } catch (...) {
+        return LBM3D_E_NOMEM;
+    }
+}
 // ---- host copies (lbm3d_api.cpp) ----
 // dst[0 .. n) = src[0 .. n), by several threads where that pays.
 void copy_host(double* dst, const double* src, size_t n);

@@ -759,7 +759,7 @@ int32_t batch_advance(lbm3d_t* hs, int32_t count, const int64_t* nsteps, hipStre
 // ------------------------------------------------------------------- C ABI --
 using namespace lbm3d;
 
-extern "C" int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
+static int32_t batch_step(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
 {
     int32_t rc = check_batch(hs, count);
     if (rc) return rc;
@@ -772,6 +772,11 @@ extern "C" int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* n
         if (hs[k]->stream != s && hipStreamSynchronize(hs[k]->stream) != hipSuccess) return LBM3D_E_DEVICE;
     BatchPlan plan;
     return batch_advance(hs, count, nsteps, s, plan, nullptr, 0, true);
+}
+
+extern "C" int32_t lbm3d_batch_step(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
+{
+    return no_throw([&] { return batch_step(hs, count, nsteps); });
 }
 
 // ------------------------------------------------ the allocation-free step --
@@ -813,7 +818,7 @@ static int32_t scratch_address(void** out)
     return LBM3D_OK;
 }
 
-extern "C" int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
+static int32_t batch_step_noalloc(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
 {
     int32_t rc = check_batch(hs, count);
     if (rc) return rc;
@@ -833,9 +838,14 @@ extern "C" int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const in
     return batch_advance(hs, count, nsteps, s, plan, ptr, NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK, false);
 }
 
-extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus,
-                                    int32_t* ntiles, int32_t* nlists, int32_t* nblocks, int32_t* tiles,
-                                    int64_t cap, int32_t* list_first)
+extern "C" int32_t lbm3d_batch_step_noalloc(lbm3d_t* hs, int32_t count, const int64_t* nsteps)
+{
+    return no_throw([&] { return batch_step_noalloc(hs, count, nsteps); });
+}
+
+static int32_t batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus,
+                          int32_t* ntiles, int32_t* nlists, int32_t* nblocks, int32_t* tiles,
+                          int64_t cap, int32_t* list_first)
 {
     if (!ps || count < 1 || cus < 1) return LBM3D_E_INVAL;
     std::vector<Grid> grids;
@@ -876,8 +886,15 @@ extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32
     return LBM3D_OK;
 }
 
-extern "C" int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
-                                      int32_t* tiled)
+extern "C" int32_t lbm3d_batch_plan(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus,
+                                    int32_t* ntiles, int32_t* nlists, int32_t* nblocks, int32_t* tiles,
+                                    int64_t cap, int32_t* list_first)
+{
+    return no_throw([&] { return batch_plan(ps, count, tz, cus, ntiles, nlists, nblocks, tiles, cap, list_first); });
+}
+
+static int32_t batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
+                            int32_t* tiled)
 {
     if (!ps || count < 1 || cus < 1 || !group || !tiled) return LBM3D_E_INVAL;
     std::vector<BatchMember> members;
@@ -898,4 +915,10 @@ extern "C" int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int
             tiled[k] = parts[j].tiled ? 1 : 0;
         }
     return LBM3D_OK;
+}
+
+extern "C" int32_t lbm3d_batch_groups(const lbm3d_params* ps, int32_t count, int32_t tz, int32_t cus, int32_t* group,
+                                      int32_t* tiled)
+{
+    return no_throw([&] { return batch_groups(ps, count, tz, cus, group, tiled); });
 }

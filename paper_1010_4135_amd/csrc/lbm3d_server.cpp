@@ -298,13 +298,13 @@ void lbm3d_server::run()
             if (fresh) {
                 const auto tp = Clock::now();
                 // (tile depth from the launch model for this membership)
-                err = plans[mode].build(members, stream, -1);
+                err = lbm3d::no_throw([&] { return plans[mode].build(members, stream, -1); });
                 plan_s += secs_since(tp);
                 rebuilds++;
                 plan_ticks[mode] = 0;
             }
             const bool graphs = plan_ticks[mode]++ >= GRAPH_AFTER_TICKS;
-            if (err == LBM3D_OK) err = plans[mode].run(k, stream, graphs, &limit);
+            if (err == LBM3D_OK) err = lbm3d::no_throw([&] { return plans[mode].run(k, stream, graphs, &limit); });
             if (err == LBM3D_OK)
                 for (Ticket* t : members_of[mode]) t->left -= std::min(k, t->left);
         }
@@ -318,7 +318,7 @@ void lbm3d_server::run()
         if (err == LBM3D_OK) (void)hipEventElapsedTime(&busy_ms, ev0, ev1);
         std::vector<uint32_t> hw_of[3];
         for (int mode = 0; mode < 3 && err == LBM3D_OK; mode++)
-            if (!members_of[mode].empty()) err = plans[mode].health(hw_of[mode], stream);
+            if (!members_of[mode].empty()) err = lbm3d::no_throw([&] { return plans[mode].health(hw_of[mode], stream); });
         std::lock_guard<std::mutex> lk(mu);
         for (int mode = 0; mode < 3; mode++) {
             for (size_t j = 0; j < members_of[mode].size(); j++) {

@@ -165,7 +165,7 @@ extern "C" int32_t lbm3d_admit(const lbm3d_params* p, const double* rho, const d
     if (!p || !rho || !ux || !uy || !uz || !pr) return LBM3D_E_INVAL;
     const int32_t v = validate(p);
     if (v != LBM3D_OK) return v;
-    return admission(p, rho, ux, uy, uz, pr, max_omega);
+    return no_throw([&] { return admission(p, rho, ux, uy, uz, pr, max_omega); });
 }
 
 extern "C" int32_t lbm3d_stability(const lbm3d_params* p, const double* q, int32_t axis, double kdx_lo,

@@ -198,7 +198,7 @@ static int32_t herr2(hipError_t e)
     return e == hipSuccess ? LBM3D_OK : (e == hipErrorOutOfMemory ? LBM3D_E_NOMEM : LBM3D_E_DEVICE);
 }
 
-extern "C" int32_t lbm3d_tune(lbm3d_t h, int32_t launches, int32_t* by, int32_t* tz)
+static int32_t tune(lbm3d_t h, int32_t launches, int32_t* by, int32_t* tz)
 {
     if (!h) return LBM3D_E_INVAL;
     if (!h->initialised) return LBM3D_E_STATE;
@@ -287,7 +287,12 @@ extern "C" int32_t lbm3d_tune(lbm3d_t h, int32_t launches, int32_t* by, int32_t*
     return LBM3D_OK;
 }
 
-extern "C" int32_t lbm3d_tune_save(const char* path)
+extern "C" int32_t lbm3d_tune(lbm3d_t h, int32_t launches, int32_t* by, int32_t* tz)
+{
+    return no_throw([&] { return tune(h, launches, by, tz); });
+}
+
+static int32_t tune_save(const char* path)
 {
     if (!path || !*path) return LBM3D_E_INVAL;
     std::lock_guard<std::mutex> lk(g_mu);
@@ -295,12 +300,22 @@ extern "C" int32_t lbm3d_tune_save(const char* path)
     return save_locked(path);
 }
 
-extern "C" int32_t lbm3d_tune_load(const char* path)
+extern "C" int32_t lbm3d_tune_save(const char* path)
+{
+    return no_throw([&] { return tune_save(path); });
+}
+
+static int32_t tune_load(const char* path)
 {
     if (!path || !*path) return LBM3D_E_INVAL;
     std::lock_guard<std::mutex> lk(g_mu);
     env_load_locked();
     return load_locked(path);
+}
+
+extern "C" int32_t lbm3d_tune_load(const char* path)
+{
+    return no_throw([&] { return tune_load(path); });
 }
 
 extern "C" int32_t lbm3d_batch_set_depth(int32_t precision, int32_t tz)
@@ -313,7 +328,7 @@ extern "C" int32_t lbm3d_batch_set_depth(int32_t precision, int32_t tz)
     return LBM3D_OK;
 }
 
-extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches, int32_t* tz)
+static int32_t batch_tune(lbm3d_t* hs, int32_t count, int32_t launches, int32_t* tz)
 {
     int32_t rc = check_batch(hs, count);
     if (rc) return rc;
@@ -418,4 +433,9 @@ extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches
     }
     if (tz) *tz = best_tz;
     return LBM3D_OK;
+}
+
+extern "C" int32_t lbm3d_batch_tune(lbm3d_t* hs, int32_t count, int32_t launches, int32_t* tz)
+{
+    return no_throw([&] { return batch_tune(hs, count, launches, tz); });
 }

@@ -1,15 +1,30 @@
 // Host-side checks of rules that choose between paths, built like the other
 // host checks with sanitizers and without kernels: how a transfer between
 // caller memory and the device goes (copy_plan), and what the batched step
-// does where the tables of its groups do not fit the room it is given.
+// does where the tables of its groups do not fit the room it is given, and
+// where the host has no memory for its plan.
 #include "../../include/lbm3d.h"
 #include "../../paper_1010_4135_amd/csrc/lbm3d_api_impl.h"
 #include "../../paper_1010_4135_amd/csrc/lbm3d_batch.h"
 #include "../../paper_1010_4135_amd/csrc/lbm3d_internal.h"
 
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <random>
+
+// The allocation that fails, counted down (negative: none).
+static long fail_at = -1;
+void* operator new(size_t n)
+{
+    if (fail_at >= 0 && fail_at-- == 0) throw std::bad_alloc();
+    if (void* p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return std::malloc(n ? n : 1); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 namespace lbm3d {
 hipError_t launch_init(int, const Grid&, const Model<double>&, const double*, void*, hipStream_t) { return hipErrorNoDevice; }
@@ -150,9 +165,38 @@ static void check_tables()
     }
 }
 
+static void check_no_memory()
+{
+    lbm3d_params ps[3];
+    const int grids[3][3] = {{192, 128, 128}, {40, 33, 20}, {128, 64, 64}};
+    for (int k = 0; k < 3; k++) {
+        lbm3d_solver h;
+        shape(h, grids[k][0], grids[k][1], grids[k][2], LBM3D_FP32);
+        ps[k] = h.p;
+        ps[k].c1 = ps[k].eta0 = 8;
+        ps[k].c2 = 24;
+        ps[k].gamma = 1.4;
+        ps[k].tau = ps[k].dt = 1e-5;
+        ps[k].dx = 1.0 / 256;
+    }
+    int32_t n = 0, group[3], tiled[3];
+    for (int which = 0; which < 2; which++) {
+        int32_t rc = LBM3D_E_NOMEM;
+        long allocations = 0;
+        for (; rc == LBM3D_E_NOMEM && allocations < 100000; allocations++) {
+            fail_at = allocations;
+            rc = which ? lbm3d_batch_groups(ps, 3, 0, 256, group, tiled)
+                       : lbm3d_batch_plan(ps, 3, -1, 256, &n, nullptr, nullptr, nullptr, 0, nullptr);
+        }
+        EXPECT(rc == LBM3D_OK && fail_at >= 0 && allocations > 3);
+        fail_at = -1;
+    }
+}
+
 int main()
 {
     std::mt19937 rng(4711);
+    check_no_memory();
     check_copies(rng);
     check_tables();
     if (failures) {
