@@ -477,7 +477,7 @@ static hipError_t refresh_layers(lbm3d_solver* h)
 // updates at 18 - 40 G/s, unless they have run since they were queued)?
 static bool stepping(lbm3d_solver* h)
 {
-    if ((h->steps - h->read_steps) * h->n < (int64_t)64 << 20) return false;
+    if ((double)(h->steps - h->read_steps) * (double)h->n < 64.0 * 1048576.0) return false;
     const bool busy = hipStreamQuery(h->stream) == hipErrorNotReady;
     (void)hipGetLastError();
     return busy;

@@ -178,8 +178,11 @@ bool stream_rows(const Grid& g, int mode)
 // 384x96x50 44.6 (49.2), FP64 100x61x50 29 (34).  Where the tiles fill 95%
 // of their rounds the two models are mostly within their own error (FP32
 // 128^3 52 and 52, 512x64x48 38.6 tiled and 39.3, 128x128x64 29.5 and 27.0)
-// and the tiles stay; 96x64x64 FP64, 37 us tiled and 28 untiled, is the
-// grid that pays for this line.
+// and the tiles stay.  96x64x64 FP64 pays for this line: 34.4 us tiled and
+// 27.8 untiled periodic, 43.1 and 30.7 with walls.  So do grids just beyond
+// the cache with walls along y or z, whose tiled step takes a layer launch of
+// 6 us more that this model leaves out: 298x78x78 FP32 with FP64 moments (274
+// MB) 67.5 us tiled and 58.6 untiled with walls, 52.5 and 52.1 periodic.
 constexpr int64_t CACHED_BYTES = (int64_t)256 << 20;
 
 TileCfg default_tile(int mode, const Grid& g)

@@ -340,7 +340,7 @@ __device__ __forceinline__ void step_tile_x(const StepArgs<MODE>& A, uint64_t at
     // The model constants.  In FP32 they are read once more in every plane:
     // held throughout, they spill the scalar file, and each plane reads some
     // 100 of its dwords back from vector lanes (256x128x128: 111.1 us a step
-    // held, 108.8 read again; 128^3 53.8 and 52.0).  A double constant takes
+    // held, 109.4 read again; 128^3 53.8 and 52.5).  A double constant takes
     // two scalar registers, and an instruction one scalar operand only, so
     // the double models gain nothing from the scalar file: the 8-row tiles
     // hold theirs in vector registers, which they have to spare at two
