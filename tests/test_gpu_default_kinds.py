@@ -17,7 +17,7 @@ TILED = [((250, 120, 33), "fp64"), ((170, 150, 100), "fp32"), ((160, 160, 160), 
 
 
 def _compute_units():
-    """Of the first GPU the kernel driver lists (four SIMDs each; 0: unknown)."""
+    """Of the first GPU in the KFD topology (four SIMDs each; 0: unknown)."""
     for f in sorted(glob.glob("/sys/class/kfd/kfd/topology/nodes/*/properties")):
         try:
             with open(f) as lines:
